@@ -41,7 +41,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E peak
 EDGES = {0: 3, 1: 6, 2: 12, 3: 4, 4: 9, 5: 8}
 NPE = {0: 3, 1: 4, 2: 8, 3: 4, 4: 6, 5: 5}
 TYPE_NAME = {0: "tri3", 1: "tet4", 2: "hex8", 3: "quad4", 4: "wedge6", 5: "pyramid5"}
-SORT_NAME = {0: "full_key", 1: "vertex_rows", 2: "edge_rows", 3: "elem_rows"}
+SORT_NAME = {-1: "library", 0: "full_key", 1: "vertex_rows", 2: "edge_rows", 3: "elem_rows"}
 PROFILES = os.path.join(ROOT, "profiles")
 
 WORKLOADS = {
@@ -81,6 +81,19 @@ def id_bits(n_vert):
     return b
 
 
+def record_words(etype, n_elem, n_vert, row_bits=9):
+    """Words of a bucket record of a call that builds the node relation
+    (buckets.hpp): the element, row_bits bits of the vertex and its
+    edge-neighbours in the element, in two or three words where they fit."""
+    k = {0: 2, 1: 3, 2: 3, 3: 2, 4: 3, 5: 4}[etype]
+    b, e = id_bits(n_vert), id_bits(n_elem)
+    if k == 2 and 2 * b + e + row_bits <= 64:
+        return 2
+    if k == 3 and 3 * b <= 64 and e + row_bits <= 32:
+        return 3
+    return k + 1
+
+
 def kernel_bytes(m, nnz_node, nnz_elem, node_sort):
     """Algorithmic HBM bytes per launch of every kernel of a step: what the
     kernel must read and write at least once.  P = directed edge pairs
@@ -91,12 +104,15 @@ def kernel_bytes(m, nnz_node, nnz_elem, node_sort):
     last one.  node_erows (rows gathered through the element relation) reads
     the element CSR and conn once and writes each row's distinct values and
     count; node_erows_scan turns the counts into row_ptr and
-    node_erows_gather moves the values into cols."""
+    node_erows_gather moves the values into cols.  The bucket kernels (the
+    library's choice) write and read one record of 4 W bytes per element pair:
+    bucket_part makes the records from conn, bucket_rows both CSRs from them."""
     f, v, k, npe = m.n_elem, m.n_vert, EDGES[m.etype], NPE[m.etype]
     p_pairs, q_pairs, u = 2 * k * f, nnz_elem, nnz_node
     keys = k * f if node_sort == 2 else p_pairs
     e = u // 2
     conn = 4 * npe * f
+    rec = 4 * q_pairs * record_words(m.etype, f, v)
     elem_passes = (id_bits(v) + 7) // 8
     csr_out = 4 * q_pairs + 4 * (v + 1)                      # cols and row starts
     later = [16 * q_pairs] * (elem_passes - 2) + [8 * q_pairs + csr_out]
@@ -120,6 +136,10 @@ def kernel_bytes(m, nnz_node, nnz_elem, node_sort):
         "node_erows": 4 * (v + 1) + 4 * q_pairs + conn + 4 * v + 4 * u,
         "node_erows_scan": 4 * v + 4 * (v + 1),
         "node_erows_gather": 8 * (v + 1) + 4 * u + 4 * u,
+        "bucket_hist": conn,
+        "bucket_scan": 0,                                   # counts per bucket and block (small)
+        "bucket_part": conn + rec,
+        "bucket_rows": rec + 4 * u + 4 * q_pairs + 8 * (v + 1),
         "hist_sum": 0,
         "elem_hist": conn,
         "elem_radix_first": conn + (8 * q_pairs if elem_passes > 1 else csr_out),
@@ -130,7 +150,7 @@ def kernel_bytes(m, nnz_node, nnz_elem, node_sort):
 
 
 # the translation unit that launches each profiled kernel
-KERNEL_UNITS = {"node_erows": "elem_rows.hip"}
+KERNEL_UNITS = {"node_erows": "elem_rows.hip", "bucket_rows": "bucket_rows.hip", "bucket_part": "bucket_path.hip"}
 
 
 def _include_closure(path):
@@ -314,7 +334,7 @@ def run_workload(name, steps, warmup, torch, nb, compare_sorts=True, e2e=True, c
     conn = torch.as_tensor(m.conn).to(dev)
     build = nb.NeighborBuild("both", m.n_elem, m.etype, m.n_vert, dev, options="tuned")
     opts = build.options.as_dict()
-    node_sort = opts["node_sort"] if opts["node_sort"] >= 0 else 3
+    node_sort = opts["node_sort"]
     stream = torch.cuda.current_stream(dev)
 
     def step():
@@ -383,7 +403,7 @@ def run_workload(name, steps, warmup, torch, nb, compare_sorts=True, e2e=True, c
         # relations (default tile shape); outputs compared byte for byte
         ref = _snapshot(build)
         by_sort = {}
-        for ns in (0, 1, 2, 3):
+        for ns in (-1, 0, 1, 2, 3):
             b = nb.NeighborBuild("both", m.n_elem, m.etype, m.n_vert, dev, options={"node_sort": ns})
             b.launch(conn, stream)
             b.check(stream)

@@ -117,7 +117,13 @@ typedef enum {
 } mesh_node_sort;
 
 /* Fields set to -1 take the library default (a rule built into the library,
- * the same for every call of the same sizes).  The workspace size depends on
+ * the same for every call of the same sizes).  With node_sort, radix_shape and
+ * digit_bits all -1, a mesh of one element type with up to about 40 elements
+ * per vertex is built from vertex buckets instead of a sort: its (vertex,
+ * element) pairs, each with the vertex's edge-neighbors in that element, are
+ * scattered once into buckets of consecutive vertices, and each bucket is
+ * finished in the LDS of one block, for both relations at once.  Naming any
+ * of the three asks for the pipelines described at mesh_node_sort.  The workspace size depends on
  * the options: query and call with the same options. */
 typedef struct {
     int32_t node_sort;    /* mesh_node_sort, or -1                               */

@@ -1,7 +1,7 @@
 """Autotuner for the library's speed-only choices.
 
-Every choice it makes changes speed only, never results: the node algorithm
-(LSD sort of the full key; sort by the vertex bits plus per-row
+Every choice it makes changes speed only, never results: the library's own
+choice (vertex buckets, where they apply), or the node algorithm (LSD sort of the full key; sort by the vertex bits plus per-row
 deduplication; each edge once by its lower vertex, deduplicated per row, then
 transposed; or rows gathered through the element relation), the radix tile
 shape (threads per block x keys per thread, which also sets the waves per
@@ -125,11 +125,12 @@ def _time(torch, build, conn, steps):
 
 
 def candidates(kind, batch=False):
-    """Every (node algorithm, tile shape, digit width) timed for a relation:
-    8-bit digits under every tuned shape, 11-bit digits (the element sort
-    only; batches sort with 8-bit digits) under the wide pass's shape."""
+    """Every choice timed for a relation: the library's own, then every (node
+    algorithm, tile shape, digit width): 8-bit digits under every tuned shape,
+    11-bit digits (the element sort only; batches sort with 8-bit digits)
+    under the wide pass's shape."""
     modes = (0, 1, 2, 3) if kind != "elem" else (-1,)
-    out = []
+    out = [{"node_sort": -1, "radix_shape": -1, "digit_bits": -1}]
     for m in modes:
         out += [{"node_sort": m, "radix_shape": s, "digit_bits": 8} for s in TUNED_SHAPES]
         if not batch and (kind != "node" or m == 3):

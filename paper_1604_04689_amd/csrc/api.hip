@@ -78,6 +78,7 @@ bool resolve_options(const mesh_options* o, Opts* out, bool allow_chunk) {
         if (o->node_sort >= 0) r.node_sort = o->node_sort;
         if (o->radix_shape >= 0) r.shape = o->radix_shape;
         r.digit_bits = o->digit_bits;
+        r.library = o->node_sort < 0 && o->radix_shape < 0 && o->digit_bits < 0;
         r.chunk_keys = o->chunk_keys > 0 ? o->chunk_keys : 0;
     }
     *out = r;
@@ -158,7 +159,10 @@ struct SinglePlans {
     ElemPlan elem;
     bool chunked = false;  // bounded-memory build (chunk_keys): `chunk` runs the call
     ChunkPlan chunk;
+    BkPlan bk;             // vertex buckets: run the call where they apply (bk.on)
 };
+
+static size_t both_bytes(const SinglePlans& sp);
 
 enum Relations { REL_NODE = 1, REL_ELEM = 2, REL_BOTH = 3 };
 
@@ -179,6 +183,11 @@ static mesh_status plan_single(int64_t n_elem, int32_t etype, int32_t n_vert, co
         if (!plan_chunked(n_elem, etype, n_vert, sp->o, (relations & REL_NODE) != 0, (relations & REL_ELEM) != 0,
                           &sp->chunk))
             return MESH_ERR_INVALID_ARG;
+    } else {
+        // in the workspace the sort pipelines need, so that a call's size does not depend on the choice
+        const size_t limit = relations == REL_BOTH ? both_bytes(*sp) : relations == REL_NODE ? sp->node.total
+                                                                                             : sp->elem.total;
+        plan_buckets(n_elem, etype, n_vert, sp->o, (relations & REL_NODE) != 0, limit, &sp->bk);
     }
     return MESH_OK;
 }
@@ -241,6 +250,9 @@ mesh_status mesh_node_neighbors(const int32_t* conn, int64_t n_elem, int32_t ety
     if (sp.chunked)
         return run_chunked(sp.chunk, conn, row_ptr, cols, cols_capacity, nullptr, nullptr, 0, workspace,
                            (hipStream_t)stream);
+    if (sp.bk.on)
+        return hip_status(run_buckets(sp.bk, conn, row_ptr, cols, cols_capacity, nullptr, nullptr, 0, workspace,
+                                      (hipStream_t)stream));
     return hip_status(run_node(sp.node, conn, row_ptr, cols, cols_capacity, workspace, (hipStream_t)stream));
 }
 
@@ -267,6 +279,9 @@ mesh_status mesh_elem_neighbors(const int32_t* conn, int64_t n_elem, int32_t ety
     if (sp.chunked)
         return run_chunked(sp.chunk, conn, nullptr, nullptr, 0, row_ptr, cols, cols_capacity, workspace,
                            (hipStream_t)stream);
+    if (sp.bk.on)
+        return hip_status(run_buckets(sp.bk, conn, nullptr, nullptr, 0, row_ptr, cols, cols_capacity, workspace,
+                                      (hipStream_t)stream));
     return hip_status(run_elem(sp.elem, conn, row_ptr, cols, cols_capacity, workspace, (hipStream_t)stream));
 }
 
@@ -308,6 +323,9 @@ mesh_status mesh_neighbors(const int32_t* conn, int64_t n_elem, int32_t etype, i
     if (sp.chunked)
         return run_chunked(sp.chunk, conn, node_row_ptr, node_cols, node_cols_capacity, elem_row_ptr, elem_cols,
                            elem_cols_capacity, workspace, s);
+    if (sp.bk.on)
+        return hip_status(run_buckets(sp.bk, conn, node_row_ptr, node_cols, node_cols_capacity, elem_row_ptr, elem_cols,
+                                      elem_cols_capacity, workspace, s));
     if (sp.node.mode == NS_ELEM_ROWS)
         return hip_status(run_node(sp.node, conn, node_row_ptr, node_cols, node_cols_capacity, workspace, s, false,
                                    elem_row_ptr, elem_cols, elem_cols_capacity));

@@ -21,6 +21,7 @@ struct Opts {
     int shape = 0;       // requested radix tile shape
     int digit_bits = -1;  // requested radix digit width (-1: the rule for the sort at hand)
     int64_t chunk_keys = 0;  // bounded-memory build: pairs sorted at once (0: the whole mesh)
+    bool library = true;     // node algorithm, tile shape and digit width all left to the library
 };
 
 // false: an option out of range (MESH_ERR_INVALID_ARG).  chunk_keys > 0 is an
@@ -145,6 +146,39 @@ hipError_t run_erows_uniform(int32_t etype, const ErowsPlan& er, const int32_t* 
                              int32_t n_vert, const int32_t* erp, const int32_t* ecols, int64_t ecap,
                              int32_t* row_ptr, int32_t* cols, int64_t cols_cap, char* ws, uint32_t* err,
                              uint32_t* ticket, hipStream_t s);
+
+// ---- vertex buckets (buckets.hpp): the library's choice where it applies -------
+// Where a vertex goes and how a record packs its element and vertex.
+struct BkMap {
+    uint32_t mul = 0;       // bucket(v) = (v * mul) >> 32
+    uint32_t n_bucket = 0;
+    uint32_t nb_pad = 0;    // n_bucket rounded up to even
+    uint32_t e_bits = 0, id_bits = 0;
+    uint32_t e_shift = 0;   // where the element starts in a 64-bit record
+    uint32_t vl_mask = 0;   // low vertex bits kept in a record
+    int32_t n_vert = 0;
+};
+struct BkPlan {
+    bool on = false;
+    int K = 0, W = 0;         // neighbours per record (0: element relation alone), words per record
+    bool large = false;       // bucket size (BkShape)
+    bool large_tile = false;  // tile size (BkTile)
+    int64_t n_elem = 0, n_slots = 0;
+    int32_t etype = 0;
+    BkMap mp;
+    int64_t n_tiles = 0;
+    int R = 1;                // tiles per bk_hist block
+    int hist_blocks = 0;
+    size_t off_flags = 0, off_scan = 0, off_starts = 0, off_rep = 0, off_lb = 0, off_btot = 0, off_within = 0, off_rec = 0;
+    size_t total = 0;
+};
+// Plans the bucket pipeline into at most `limit` workspace bytes; p->on says
+// whether it applies.  node: the node relation is wanted.
+void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, bool node, size_t limit, BkPlan* p);
+// Outputs of a relation that is not wanted are null.
+hipError_t run_buckets(const BkPlan& p, const int32_t* conn, int32_t* node_row_ptr, int32_t* node_cols,
+                       int64_t node_cap, int32_t* elem_row_ptr, int32_t* elem_cols, int64_t elem_cap, void* ws,
+                       hipStream_t s);
 
 // ---- bounded-memory build (chunk_keys) ------------------------------------------
 // The relations of one mesh of one type, one vertex range at a time: a
