@@ -7,6 +7,7 @@
 #include "common.hpp"
 #include "elements.hpp"
 #include "internal.hpp"
+#include "bucket_batch.hpp"
 #include "launch.hpp"
 #include "radix.hpp"
 
@@ -392,7 +393,10 @@ struct BatchPlans {
     Opts o;
     BatchNodePlan node;
     BatchPlan elem;
+    BkBatchPlan bk;  // vertex buckets: run the call where they apply (bk.on)
 };
+
+static size_t batch_both_bytes(const BatchPlans& bp);
 
 static mesh_status plan_batch_call(int32_t n_mesh, int64_t total_pairs, int64_t total_slots, int32_t total_vert,
                                    int32_t max_vert, const mesh_options* opts, bool node_internal_elem,
@@ -403,6 +407,8 @@ static mesh_status plan_batch_call(int32_t n_mesh, int64_t total_pairs, int64_t 
     if (!plan_batch_node(total_pairs, total_slots, total_vert, max_vert, bp->o, node_internal_elem, &bp->node))
         return MESH_ERR_OVERFLOW;
     if (!plan_batch_elem(total_slots, total_vert, bp->o, &bp->elem)) return MESH_ERR_OVERFLOW;
+    plan_batch_buckets(n_mesh, total_pairs, total_slots, total_vert, max_vert, bp->o,
+                       node_internal_elem ? bp->node.total : batch_both_bytes(*bp), &bp->bk);
     return MESH_OK;
 }
 
@@ -430,6 +436,9 @@ mesh_status mesh_batch_node_neighbors(const int32_t* conn, const mesh_segment* s
         return MESH_ERR_INVALID_ARG;
     st = workspace_ok(workspace, workspace_bytes, bp.node.total);
     if (st != MESH_OK) return st;
+    if (bp.bk.on)
+        return hip_status(run_batch_buckets(bp.bk, conn, segs, row_ptr, cols, cols_capacity, nullptr, nullptr, 0,
+                                            workspace, (hipStream_t)stream));
     return hip_status(run_batch_node(bp.node, conn, segs, n_mesh, batch_node_lo_bits(max_vert), total_vert, row_ptr,
                                      cols, cols_capacity, workspace, (hipStream_t)stream));
 }
@@ -501,6 +510,9 @@ mesh_status mesh_batch_neighbors(const int32_t* conn, const mesh_segment* segs, 
     st = workspace_ok(workspace, workspace_bytes, batch_both_bytes(bp));
     if (st != MESH_OK) return st;
     hipStream_t s = (hipStream_t)stream;
+    if (bp.bk.on)
+        return hip_status(run_batch_buckets(bp.bk, conn, segs, node_row_ptr, node_cols, node_cols_capacity,
+                                            elem_row_ptr, elem_cols, elem_cols_capacity, workspace, s));
     const uint32_t lo = batch_node_lo_bits(max_vert);
     if (bp.node.mode == NS_ELEM_ROWS)
         return hip_status(run_batch_node(bp.node, conn, segs, n_mesh, lo, total_vert, node_row_ptr, node_cols,

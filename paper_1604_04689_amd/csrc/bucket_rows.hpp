@@ -865,31 +865,19 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
     return true;
 }
 
+// Bucket `bucket` (n records from rec0 on, the r0-th pair of all): both its
+// relations.  Every thread of the block calls it.
 template <int K, int W, bool LARGE>
-__global__ __launch_bounds__((BkShape<K, LARGE>::BLOCK)) __attribute__((amdgpu_waves_per_eu(4)))
-void bk_rows_kernel(BkRowsArgs a) {
+__device__ __forceinline__ void bk_bucket_rows(const BkRowsArgs& a, uint32_t bucket, int64_t rec0, uint32_t n,
+                                               uint32_t r0, uint32_t lo, int nv, uint32_t odd, uint32_t* s_all,
+                                               uint32_t* s_tmp, uint64_t* s_base) {
     using S = BkShape<K, LARGE>;
     using L = BkLds<K, LARGE>;
-    __shared__ __align__(16) uint32_t s_all[L::WORDS];
     uint32_t* const s_val = s_all;
     uint32_t* const s_start = s_val + L::VAL;       // row starts
     uint32_t* const s_cnt = s_start + S::VMAX + 1;  // distinct neighbours, then their offsets
     uint16_t* const s_pos = reinterpret_cast<uint16_t*>(s_cnt + S::VMAX + 1);  // bk_ranges
-    __shared__ uint32_t s_tmp[2 * (S::BLOCK / WAVE)];
-    __shared__ uint32_t s_bucket;
-    __shared__ uint64_t s_base;
     const int tid = threadIdx.x;
-    if (tid == 0) s_bucket = atomicAdd(&a.hdr[HDR_BK_TICKET], 1u);  // so that every earlier bucket is already running
-    __syncthreads();
-    // the same for every thread: scalar registers
-    const uint32_t bucket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bucket);
-    const uint32_t odd = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.hdr[HDR_BK_ODD]);
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket]);
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket + 1]) - r0;
-    const int64_t rec0 = r0;
-    const uint32_t lo = bk_first_vertex(bucket, a.mp.mul);
-    const uint32_t hi = bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_first_vertex(bucket + 1, a.mp.mul);
-    const int nv = (int)(hi - lo);
     if (nv < 0 || nv > S::VMAX) {  // never: the plan keeps a bucket's vertices below VMAX
         if (tid == 0) set_error(a.hdr + HDR_ERR, ERR_INTERNAL);
         return;
@@ -910,12 +898,32 @@ void bk_rows_kernel(BkRowsArgs a) {
     bool done = false;
     if (here)
         done = bk_rows_lds<K, W, LARGE>(a, bucket, rec0, n, lo, nv, odd, elem && !repeats, ebase, s_val, s_start, s_cnt,
-                                        s_tmp, &turn, &s_base);
+                                        s_tmp, &turn, s_base);
     if (K > 0 && node && !done)
-        bk_ranges<K, W, LARGE>(a, false, bucket, rec0, n, lo, nv, 0, s_val, s_start, s_cnt, s_pos, s_tmp, &turn, &s_base);
+        bk_ranges<K, W, LARGE>(a, false, bucket, rec0, n, lo, nv, 0, s_val, s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
     if (elem && (!done || repeats))
         bk_ranges<K, W, LARGE>(a, true, bucket, rec0, n, lo, nv, ebase, s_val, s_start, s_cnt, s_pos, s_tmp, &turn,
-                               &s_base);
+                               s_base);
+}
+
+template <int K, int W, bool LARGE>
+__global__ __launch_bounds__((BkShape<K, LARGE>::BLOCK)) __attribute__((amdgpu_waves_per_eu(4)))
+void bk_rows_kernel(BkRowsArgs a) {
+    using S = BkShape<K, LARGE>;
+    __shared__ __align__(16) uint32_t s_all[BkLds<K, LARGE>::WORDS];
+    __shared__ uint32_t s_tmp[2 * (S::BLOCK / WAVE)];
+    __shared__ uint32_t s_bucket;
+    __shared__ uint64_t s_base;
+    if (threadIdx.x == 0) s_bucket = atomicAdd(&a.hdr[HDR_BK_TICKET], 1u);  // so that every earlier bucket is already running
+    __syncthreads();
+    // the same for every thread: scalar registers
+    const uint32_t bucket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bucket);
+    const uint32_t odd = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.hdr[HDR_BK_ODD]);
+    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket]);
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket + 1]) - r0;
+    const uint32_t lo = bk_first_vertex(bucket, a.mp.mul);
+    const uint32_t hi = bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_first_vertex(bucket + 1, a.mp.mul);
+    bk_bucket_rows<K, W, LARGE>(a, bucket, r0, n, r0, lo, (int)(hi - lo), odd, s_all, s_tmp, &s_base);
 }
 
 }  // namespace mnb

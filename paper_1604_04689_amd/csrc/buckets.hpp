@@ -83,7 +83,7 @@ __device__ __forceinline__ uint32_t bk_bucket(uint32_t v, uint32_t mul) { return
 //   K = 3, W = 3     the neighbours in 64 bits, the element and the vertex in 32
 //   K = 2, W = 2     all in 64 bits
 //   K = 0            element and vertex in one word, or a word each
-inline int bk_words(int K, uint32_t e_bits, uint32_t id_bits, uint32_t vl_bits) {
+__host__ __device__ inline int bk_words(int K, uint32_t e_bits, uint32_t id_bits, uint32_t vl_bits) {
     if (K == 0) return e_bits + vl_bits <= 32 ? 1 : 2;
     if (K == 2 && e_bits + vl_bits + 2 * id_bits <= 64) return 2;
     if (K == 3 && 3 * id_bits <= 64 && e_bits + vl_bits <= 32) return 3;
@@ -319,53 +319,45 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
 }
 
 // ---- bk_part ---------------------------------------------------------------------
-// Tile t = blockIdx.x.  Its records' buckets are counted (each record keeps
-// its place among the tile's records of that bucket), the counts scanned, the
-// records put in bucket order in LDS and written out: consecutive lanes write
-// consecutive records, a run per bucket.  A slot whose id is out of range has
-// no record; a neighbour that is out of range or the vertex itself is stored
-// as the vertex, which its row drops.  Bound by the writes' lines: 25.1 M
-// records of 12 bytes (100 MB in, 302 MB out), 112 / 154 / 199 us for 1024 /
-// 2048 / 4096 buckets (runs of 108 / 54 / 27 bytes).
-template <int ET, int K, int W, int BLOCK, int EPT>
-__global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restrict__ conn, int64_t n_elem, BkMap mp,
-                                                       int R, const uint16_t* __restrict__ within,
-                                                       const uint32_t* __restrict__ btot,
-                                                       const uint32_t* __restrict__ starts,
-                                                       uint32_t* __restrict__ rec, int64_t rec_cap,
-                                                       uint32_t* repeats, uint32_t* hdr) {
+// Elements [e0, e0 + count) of a tile.  Its records' buckets are counted (each
+// record keeps its place among the tile's records of that bucket), the counts
+// scanned, the records put in bucket order in LDS and written out: consecutive
+// lanes write consecutive records, a run per bucket, bucket b's from first(b)
+// on.  A slot whose id is out of range has no record; a neighbour that is out
+// of range or the vertex itself is stored as the vertex, which its row drops.
+// s_dyn: two words per bucket, the records, a 16-bit bucket number each.
+template <int ET, int K, int W, int BLOCK, int EPT, class First>
+__device__ __forceinline__ void bk_part_tile(const int32_t* __restrict__ conn, int64_t e0, int32_t count,
+                                             const BkMap& mp, First&& first, uint32_t* __restrict__ rec,
+                                             int64_t rec_cap, uint32_t* repeats, uint32_t* hdr, uint32_t* s_dyn,
+                                             uint32_t* s_tmp) {
     using E = BkElem<ET>;
     constexpr int NPE = E::NPE;
     constexpr int T = BLOCK * EPT * NPE;
-    constexpr int WAVES = BLOCK / WAVE;
     static_assert(T <= 65535, "16-bit places");
-    extern __shared__ uint32_t s_dyn[];
     const int nb = (int)mp.nb_pad;
     uint32_t* const s_cnt = s_dyn;        // counts, then offsets
     uint32_t* const s_glob = s_dyn + nb;  // where the bucket's first record goes, less its offset
     uint32_t* const s_rec = s_glob + nb;
-    uint16_t* const s_b = reinterpret_cast<uint16_t*>(s_rec + T * W);
-    __shared__ uint32_t s_tmp[WAVES];
+    uint16_t* const s_b = reinterpret_cast<uint16_t*>(s_rec + count * NPE * W);
     const int tid = threadIdx.x;
     const bool dup = (hdr[HDR_BK_ODD] & BK_HAS_DUP) != 0;
-    const int64_t t = blockIdx.x;
-    const int64_t h = (t / BK_XCDS / R) * BK_XCDS + t % BK_XCDS;
     int32_t id[EPT][NPE] = {};
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
-        const int64_t e = t * (BLOCK * EPT) + u * BLOCK + tid;
-        if (e < n_elem) load_elem_ids<ET>(conn, e, id[u]);
+        const int32_t i = u * BLOCK + tid;
+        if (i < count) load_elem_ids<ET>(conn, e0 + i, id[u]);
     }
     for (int i = tid; i < nb; i += BLOCK) {
         s_cnt[i] = 0;
-        s_glob[i] = i < (int)mp.n_bucket ? starts[i] + btot[h * nb + i] + within[t * nb + i] : 0u;
+        s_glob[i] = i < (int)mp.n_bucket ? first(i) : 0u;
     }
     __syncthreads();
     uint32_t place[EPT][(NPE + 1) / 2] = {};  // two 16-bit places per word
     const bool crowded = bk_crowded(bk_bucket((uint32_t)id[0][0], mp.mul));
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
-        const bool in = t * (BLOCK * EPT) + u * BLOCK + tid < n_elem;
+        const bool in = u * BLOCK + tid < count;
 #pragma unroll
         for (int j = 0; j < NPE; ++j) {
             const uint32_t v = (uint32_t)id[u][j];
@@ -395,11 +387,11 @@ __global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restric
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
-        const int64_t e = t * (BLOCK * EPT) + u * BLOCK + tid;
+        const int32_t i = u * BLOCK + tid;
 #pragma unroll
         for (int j = 0; j < NPE; ++j) {
             const uint32_t v = (uint32_t)id[u][j];
-            if (e >= n_elem || v >= (uint32_t)mp.n_vert) continue;
+            if (i >= count || v >= (uint32_t)mp.n_vert) continue;
             const uint32_t b = bk_bucket(v, mp.mul);
             const uint32_t p = s_cnt[b] + ((place[u][j / 2] >> (16 * (j & 1))) & 0xffffu);
             if (dup) {  // (seldom: some element of the mesh repeats an id)
@@ -415,7 +407,7 @@ __global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restric
                 nbr[k] = w < (uint32_t)mp.n_vert ? w : v;
             }
             uint32_t r[W];
-            bk_encode<K, W>(mp, (uint32_t)e, v, nbr, r);
+            bk_encode<K, W>(mp, (uint32_t)(e0 + i), v, nbr, r);
 #pragma unroll
             for (int q = 0; q < W; ++q) s_rec[p * W + q] = r[q];
             s_b[p] = (uint16_t)b;
@@ -435,6 +427,27 @@ __global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restric
         else bad = true;  // only if conn changed under the call
     }
     if (bad) set_error(hdr + HDR_ERR, ERR_INTERNAL);
+}
+
+// Tile t = blockIdx.x.  Bound by the writes' lines: 25.1 M records of 12 bytes
+// (100 MB in, 302 MB out), 112 / 154 / 199 us for 1024 / 2048 / 4096 buckets
+// (runs of 108 / 54 / 27 bytes).
+template <int ET, int K, int W, int BLOCK, int EPT>
+__global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restrict__ conn, int64_t n_elem, BkMap mp,
+                                                       int R, const uint16_t* __restrict__ within,
+                                                       const uint32_t* __restrict__ btot,
+                                                       const uint32_t* __restrict__ starts,
+                                                       uint32_t* __restrict__ rec, int64_t rec_cap,
+                                                       uint32_t* repeats, uint32_t* hdr) {
+    constexpr int TE = BLOCK * EPT;
+    extern __shared__ uint32_t s_dyn[];
+    __shared__ uint32_t s_tmp[BLOCK / WAVE];
+    const int64_t t = blockIdx.x;
+    const int64_t h = (t / BK_XCDS / R) * BK_XCDS + t % BK_XCDS;
+    const int nb = (int)mp.nb_pad;
+    bk_part_tile<ET, K, W, BLOCK, EPT>(
+        conn, t * TE, (int32_t)tmin<int64_t>(n_elem - t * TE, TE), mp,
+        [&](int b) { return starts[b] + btot[h * nb + b] + within[t * nb + b]; }, rec, rec_cap, repeats, hdr, s_dyn, s_tmp);
 }
 
 // The tile shapes: threads x elements per thread.  A large tile fills most of
