@@ -20,7 +20,7 @@ OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmeshnbr.so")
 SOURCES = ["api.hip", "node_path.hip", "elem_path.hip", "elem_rows.hip", "mixed_path.hip", "batch_path.hip",
            "graph.hip", "timing.hip", "noalloc.hip", "chunk_path.hip", "bucket_path.hip", "bucket_rows.hip", "bucket_batch.hip",
-           "bucket_batch_rows.hip"]
+           "bucket_batch_rows.hip", "bucket_mixed.hip"]
 ARCH = os.environ.get("MESHNBR_ARCH", "gfx950")
 
 

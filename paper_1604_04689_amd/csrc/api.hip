@@ -375,6 +375,11 @@ mesh_status mesh_mixed_neighbors(const int32_t* conn, const int32_t* elem_off, c
         return MESH_ERR_INVALID_ARG;
     st = workspace_ok(workspace, workspace_bytes, p.total);
     if (st != MESH_OK) return st;
+    BkPlan bk;  // vertex buckets, in the workspace the sort needs
+    plan_mixed_buckets(n_elem, n_ids, n_vert, p.opts, p.total, &bk);
+    if (bk.on)
+        return hip_status(run_mixed_buckets(bk, conn, elem_off, etypes, node_row_ptr, node_cols, node_cols_capacity,
+                                            elem_row_ptr, elem_cols, elem_cols_capacity, workspace, (hipStream_t)stream));
     return hip_status(run_mixed(p, conn, elem_off, etypes, node_row_ptr, node_cols, node_cols_capacity, elem_row_ptr,
                                 elem_cols, elem_cols_capacity, workspace, (hipStream_t)stream));
 }

@@ -29,29 +29,25 @@ size_t part_lds(int npe, int W, int64_t elems, uint32_t nb_pad) {
 
 }  // namespace
 
-void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, bool node, size_t limit, BkPlan* p) {
-    *p = BkPlan{};
-    const int npe = nodes_per_elem(etype);
-    const int64_t n_slots = (int64_t)npe * n_elem;
-    if (!o.library || n_slots < 1 || n_vert < 1) return;
+bool plan_bucket_map(int64_t n_elem, int64_t n_slots, int32_t n_vert, int K, int full, BkPlan* p) {
+    if (n_slots < 1 || n_elem < 1 || n_vert < 1) return false;
     // rows much longer than any mesh's go to the sorts: the networks take up
     // to 32 (node) and 64 (element) values (tetrahedra average 24 elements)
-    if (n_slots > (int64_t)BK_MAX_DEGREE * n_vert) return;
+    if (n_slots > (int64_t)BK_MAX_DEGREE * n_vert) return false;
     p->n_elem = n_elem;
     p->n_slots = n_slots;
-    p->etype = etype;
-    p->K = node ? bk_neighbours(etype) : 0;
+    p->K = K;
     BkMap& m = p->mp;
     m.n_vert = n_vert;
     m.e_bits = bits_for_count(n_elem);
     m.id_bits = id_bits_for(n_vert);
     // buckets: small ones while a few rounds of them fill the GPU, then large
-    // ones (fewer runs in the partition); 92 % full on average
+    // ones (fewer runs in the partition)
     int64_t nb = 0;
     int vmax = 0;
     for (int large = 0; large < 2; ++large) {
         const BkSize z = bk_size(p->K, large != 0);
-        nb = tmax<int64_t>(ceil_div(n_slots * 100, (int64_t)z.cap * 92), ceil_div(n_vert, z.vmax - 2));
+        nb = tmax<int64_t>(ceil_div(n_slots * 100, (int64_t)z.cap * full), ceil_div(n_vert, z.vmax - 2));
         vmax = z.vmax;
         p->large = large != 0;
         if (nb <= BK_SMALL_MOST) break;
@@ -68,19 +64,18 @@ void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, 
     m.n_bucket = (uint32_t)(((uint64_t)(n_vert - 1) * m.mul) >> 32) + 1;
     m.nb_pad = (m.n_bucket + 1) & ~1u;
     const uint64_t widest = (((uint64_t)1 << 32) + m.mul - 1) / m.mul;
-    if ((int64_t)widest > vmax) return;
+    if ((int64_t)widest > vmax) return false;
     const uint32_t vl_bits = pow2_bits(widest);
     m.vl_mask = (1u << vl_bits) - 1;
     p->W = bk_words(p->K, m.e_bits, m.id_bits, vl_bits);
-    if (p->W == 0) return;
     m.e_shift = 2 * m.id_bits + vl_bits;
-    // tiles: large ones once they occupy every CU
-    const int64_t big = with_type(etype, [](auto et) { return (int64_t)tile_elems<decltype(et)::value>(true); });
-    p->large_tile = n_elem >= big * BK_CUS && part_lds(npe, p->W, big, m.nb_pad) <= (size_t)BK_LDS;
-    const int64_t te = p->large_tile ? big : BK_SMALL_BLOCK;
-    if (part_lds(npe, p->W, te, m.nb_pad) > (size_t)BK_LDS) return;
-    p->n_tiles = ceil_div(n_elem, te);
-    const int64_t r_most = 65535 / (te * npe);  // 16-bit counts before a tile
+    return p->W != 0;
+}
+
+void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* p) {
+    const BkMap& m = p->mp;
+    p->n_tiles = ceil_div(p->n_elem, tile_elems);
+    const int64_t r_most = 65535 / (tile_elems * most_npe);  // 16-bit counts before a tile
     p->R = (int)tmax<int64_t>(1, tmin<int64_t>(ceil_div(p->n_tiles, BK_HIST_BLOCKS), r_most));
     const int64_t blocks = BK_XCDS * ceil_div(p->n_tiles, (int64_t)BK_XCDS * p->R);
     if (blocks > BK_HIST_MOST) return;
@@ -101,9 +96,23 @@ void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, 
     p->off_within = off;
     off += align_up((size_t)p->n_tiles * m.nb_pad * sizeof(uint16_t));
     p->off_rec = off;
-    off += align_up(((size_t)n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
+    off += align_up(((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
     p->total = off;
     p->on = off <= limit;
+}
+
+void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, bool node, size_t limit, BkPlan* p) {
+    *p = BkPlan{};
+    const int npe = nodes_per_elem(etype);
+    if (!o.library || !plan_bucket_map(n_elem, (int64_t)npe * n_elem, n_vert, node ? bk_neighbours(etype) : 0, BK_FULL, p))
+        return;
+    p->etype = etype;
+    // tiles: large ones once they occupy every CU
+    const int64_t big = with_type(etype, [](auto et) { return (int64_t)tile_elems<decltype(et)::value>(true); });
+    p->large_tile = n_elem >= big * BK_CUS && part_lds(npe, p->W, big, p->mp.nb_pad) <= (size_t)BK_LDS;
+    const int64_t te = p->large_tile ? big : BK_SMALL_BLOCK;
+    if (part_lds(npe, p->W, te, p->mp.nb_pad) > (size_t)BK_LDS) return;
+    plan_bucket_layout(te, npe, limit, p);
 }
 
 namespace {
@@ -131,8 +140,8 @@ hipError_t launch_tiles(const BkPlan& p, const int32_t* conn, char* w, hipStream
     if (e == hipSuccess)
         e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)ceil_div(p.mp.n_bucket, BKS_COLS)), dim3(BKS_BLOCK), s,
                    btot, p.hist_blocks, p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags,
-                   (uint64_t*)(w + p.off_scan), (uint32_t*)(w + p.off_starts), (uint64_t*)(w + p.off_lb),
-                   (uint32_t*)(w + p.off_rep), hdr);
+                   (uint64_t*)(w + p.off_scan), (uint32_t*)(w + p.off_starts), (uint32_t)p.n_slots,
+                   (uint64_t*)(w + p.off_lb), (uint32_t*)(w + p.off_rep), hdr);
     if (e != hipSuccess) return e;
     if (p.K == 0)
         return p.W == 1 ? launch_part<ET, 0, 1, LT>(p, conn, w, s) : launch_part<ET, 0, 2, LT>(p, conn, w, s);

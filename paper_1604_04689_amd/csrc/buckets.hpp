@@ -250,7 +250,7 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
                                                                   uint32_t n_bucket, uint32_t nb_pad,
                                                                   const uint32_t* __restrict__ flags,
                                                                   uint64_t* scan_lb, uint32_t* __restrict__ starts,
-                                                                  uint64_t* __restrict__ lookback,
+                                                                  uint32_t rec_cap, uint64_t* __restrict__ lookback,
                                                                   uint32_t* __restrict__ repeats, uint32_t* hdr) {
     __shared__ uint32_t s_sum[BKS_ROWS][BKS_COLS + 1];
     __shared__ uint32_t s_tot[BKS_COLS];
@@ -302,8 +302,10 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
         if (lane == 0) lb_store(scan_lb + block, (block == 0 ? LB_INC : LB_AGG) | (uint64_t)all);
         const uint32_t before = (uint32_t)wave_lookback_prefix(scan_lb, block, all, hdr + HDR_ERR);
         if (have) {
-            starts[b] = before + incl - t;
-            if (b + 1 == n_bucket) starts[n_bucket] = before + incl;
+            // (never more than the records there is room for, which overlapping
+            // elements of an ill-formed mixed mesh could ask for)
+            starts[b] = tmin(before + incl - t, rec_cap);
+            if (b + 1 == n_bucket) starts[n_bucket] = tmin(before + incl, rec_cap);
             lookback[b] = 0;  // bk_rows'
             repeats[b] = 0;   // counted by bk_part
         }
@@ -319,6 +321,52 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
 }
 
 // ---- bk_part ---------------------------------------------------------------------
+// A tile's counts become offsets in it, in place, and each bucket's first place
+// loses its offset; returns the tile's records.  Starts and ends with a barrier.
+template <int BLOCK>
+__device__ __forceinline__ uint32_t bk_tile_offsets(uint32_t* s_cnt, uint32_t* s_glob, int nb, uint32_t* s_tmp) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    const int per = (nb + BLOCK - 1) / BLOCK;  // a thread takes consecutive buckets
+    uint32_t sum = 0;
+    for (int i = 0; i < per; ++i) {
+        const int b = tid * per + i;
+        if (b < nb) sum += s_cnt[b];
+    }
+    uint32_t total;
+    uint32_t run = block_exclusive_sum<BLOCK>(sum, s_tmp, &total);
+    for (int i = 0; i < per; ++i) {
+        const int b = tid * per + i;
+        if (b < nb) {
+            const uint32_t c = s_cnt[b];
+            s_cnt[b] = run;
+            s_glob[b] -= run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    return total;
+}
+// A tile's records, in bucket order in the LDS, to their places.  False if one
+// is beyond the room for records.
+template <int W, int BLOCK>
+__device__ __forceinline__ bool bk_tile_out(const uint32_t* s_rec, const uint16_t* s_b, const uint32_t* s_glob,
+                                            uint32_t total, uint32_t* __restrict__ rec, int64_t rec_cap) {
+    struct Words {
+        uint32_t w[W];
+    };
+    bool fits = true;
+    for (uint32_t i = threadIdx.x; i < total; i += BLOCK) {
+        const uint32_t d = s_glob[s_b[i]] + i;
+        Words r;
+#pragma unroll
+        for (int q = 0; q < W; ++q) r.w[q] = s_rec[i * W + q];
+        if ((int64_t)d < rec_cap) reinterpret_cast<Words*>(rec)[d] = r;
+        else fits = false;
+    }
+    return fits;
+}
+
 // Elements [e0, e0 + count) of a tile.  Its records' buckets are counted (each
 // record keeps its place among the tile's records of that bucket), the counts
 // scanned, the records put in bucket order in LDS and written out: consecutive
@@ -365,26 +413,7 @@ __device__ __forceinline__ void bk_part_tile(const int32_t* __restrict__ conn, i
             place[u][j / 2] |= bk_count(s_cnt, ok ? bk_bucket(v, mp.mul) : 0u, ok, crowded) << (16 * (j & 1));
         }
     }
-    __syncthreads();
-    // offsets: a thread takes consecutive buckets
-    const int per = (nb + BLOCK - 1) / BLOCK;
-    uint32_t sum = 0;
-    for (int i = 0; i < per; ++i) {
-        const int b = tid * per + i;
-        if (b < nb) sum += s_cnt[b];
-    }
-    uint32_t total;
-    uint32_t run = block_exclusive_sum<BLOCK>(sum, s_tmp, &total);
-    for (int i = 0; i < per; ++i) {
-        const int b = tid * per + i;
-        if (b < nb) {
-            const uint32_t c = s_cnt[b];
-            s_cnt[b] = run;
-            s_glob[b] -= run;
-            run += c;
-        }
-    }
-    __syncthreads();
+    const uint32_t total = bk_tile_offsets<BLOCK>(s_cnt, s_glob, nb, s_tmp);
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
         const int32_t i = u * BLOCK + tid;
@@ -414,19 +443,8 @@ __device__ __forceinline__ void bk_part_tile(const int32_t* __restrict__ conn, i
         }
     }
     __syncthreads();
-    struct Words {
-        uint32_t w[W];
-    };
-    bool bad = false;
-    for (uint32_t i = tid; i < total; i += BLOCK) {
-        const uint32_t d = s_glob[s_b[i]] + i;
-        Words r;
-#pragma unroll
-        for (int q = 0; q < W; ++q) r.w[q] = s_rec[i * W + q];
-        if ((int64_t)d < rec_cap) reinterpret_cast<Words*>(rec)[d] = r;
-        else bad = true;  // only if conn changed under the call
-    }
-    if (bad) set_error(hdr + HDR_ERR, ERR_INTERNAL);
+    // (beyond it only if conn changed under the call)
+    if (!bk_tile_out<W, BLOCK>(s_rec, s_b, s_glob, total, rec, rec_cap)) set_error(hdr + HDR_ERR, ERR_INTERNAL);
 }
 
 // Tile t = blockIdx.x.  Bound by the writes' lines: 25.1 M records of 12 bytes
