@@ -32,6 +32,9 @@ constexpr int BKB_MESHES = 2048;
 constexpr int BKB_MESH_SLOTS = 1400;
 constexpr int BKB_TILE_LEAST = 512;    // fewest slots a tile is cut for
 constexpr int BKB_SETUP = 1024;
+// Most small buckets of a batch: 1.4 M slots took 77 us in small ones, 80 us in
+// large ones, which are not rounded up to whole rounds here.
+constexpr int BKB_SMALL_MOST = 1024;
 
 constexpr int bkb_K(int32_t et) { return et == TRI3 || et == QUAD4 ? 2 : et == PYR5 ? 4 : 3; }
 static_assert(bkb_K(TRI3) == BkElem<TRI3>::K && bkb_K(QUAD4) == BkElem<QUAD4>::K && bkb_K(TET4) == BkElem<TET4>::K &&
@@ -466,7 +469,7 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
             fill_least = tmin(fill_least, p->fill[K]);
             vmax_least = tmin(vmax_least, z.vmax - 2);
         }
-        if (ceil_div(total_slots, (int64_t)fill_least) <= BK_SMALL_MOST) break;
+        if (ceil_div(total_slots, (int64_t)fill_least) <= BKB_SMALL_MOST) break;
     }
     const int64_t nb_most = tmax<int64_t>(ceil_div(max_vert, (int64_t)vmax_least),
                                           ceil_div((int64_t)max_vert * BK_MAX_DEGREE, (int64_t)fill_least)) + 1;

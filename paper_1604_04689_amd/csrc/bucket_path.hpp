@@ -7,7 +7,12 @@ namespace mnb {
 
 constexpr int BK_CUS = 256;            // CUs of the GPU
 constexpr int BK_MAX_DEGREE = 40;      // most elements per vertex, on average, of a mesh that takes buckets
-constexpr int BK_SMALL_MOST = 1024;    // most small buckets
+// Most small buckets of a mesh.  More of them run in several rounds, and large
+// ones have twice the threads to a bucket: 512 large buckets took 54 / 50 / 61 us
+// where 566 / 566 / 850 small ones took 57 / 55 / 71 us (hexahedra 55^3, their
+// node relation, 63^3); 512 half-empty large ones lose below (tetrahedra 32^3:
+// 54 us against 51 us in 334 small ones).
+constexpr int BK_SMALL_MOST = 448;
 constexpr int BK_LEAST_RECORDS = 384;  // fewest records a bucket of a small mesh is planned for
 // Records of a bucket, percent of what it holds, on average: a bucket with more
 // than it holds is finished from memory, and every later one waits for it.  The
