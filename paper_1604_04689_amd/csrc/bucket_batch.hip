@@ -463,7 +463,7 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
         fill_least = vmax_least = INT32_MAX;
         for (int K = 2; K <= 4; ++K) {
             const BkSize z = bk_size(K, large != 0);
-            p->fill[K] = z.cap * BK_FULL / 100;
+            p->fill[K] = z.cap * (K == 4 ? BK_FULL_PYRAMID : BK_FULL) / 100;
             // few records still spread over the CUs
             if (!large) p->fill[K] = (int32_t)tmin<int64_t>(p->fill[K], tmax<int64_t>(BK_LEAST_RECORDS, total_slots / BK_CUS));
             fill_least = tmin(fill_least, p->fill[K]);

@@ -9,9 +9,13 @@ namespace mnb {
 
 namespace {
 
-// Threads, and elements, of a tile: two tiles' records (22 bytes each with
-// their bucket's number, eight per element) fit a CU's LDS.
-constexpr int BKX_BLOCK = 320;
+// Threads, and elements, of a tile: the records (22 bytes each with their
+// bucket's number, eight per element) of two small tiles fit a CU's LDS, or of
+// one large one, for many buckets (longer runs of records: a
+// hybrid mesh of 3.25 M ids took 248 us in small tiles and 2048 buckets, 197 us
+// in large ones and 1612 buckets).
+constexpr int BKX_SMALL = 320, BKX_LARGE = 640;
+constexpr uint32_t BKX_SMALL_BUCKETS = 1024;
 constexpr int BKX_K = 4, BKX_W = 5;
 constexpr int BKX_IDS = MAX_NPE + 1;  // words of an element's ids in the LDS (odd: no bank conflicts)
 
@@ -62,7 +66,8 @@ __device__ __forceinline__ int bkx_load(const MixedConn& c, int64_t e, int32_t (
 }
 
 // As bk_hist, a thread per element.
-__global__ __launch_bounds__(BKX_BLOCK) void bkx_hist_kernel(MixedConn c, BkMap mp, int64_t n_tiles, int R,
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void bkx_hist_kernel(MixedConn c, BkMap mp, int64_t n_tiles, int R,
                                                             uint16_t* __restrict__ within, uint32_t* __restrict__ btot,
                                                             uint32_t* __restrict__ flags, uint64_t* __restrict__ scan_lb,
                                                             int n_scan, uint32_t* __restrict__ hdr) {
@@ -70,11 +75,11 @@ __global__ __launch_bounds__(BKX_BLOCK) void bkx_hist_kernel(MixedConn c, BkMap 
     __shared__ uint32_t s_flags;
     const int tid = threadIdx.x;
     const int nb = (int)mp.nb_pad;
-    for (int i = tid; i < nb; i += BKX_BLOCK) s_h[i] = 0;
+    for (int i = tid; i < nb; i += BLOCK) s_h[i] = 0;
     if (tid == 0) s_flags = 0;
     if (blockIdx.x == 0) {  // what the later kernels need at zero
         if (tid < (int)(HEADER_BYTES / 4)) hdr[tid] = 0;
-        for (int i = tid; i < n_scan; i += BKX_BLOCK) scan_lb[i] = 0;
+        for (int i = tid; i < n_scan; i += BLOCK) scan_lb[i] = 0;
     }
     __syncthreads();
     uint32_t found = 0;
@@ -85,10 +90,10 @@ __global__ __launch_bounds__(BKX_BLOCK) void bkx_hist_kernel(MixedConn c, BkMap 
         int32_t id[MAX_NPE];
         uint32_t type;
         bool odd = false;
-        const int npe = bkx_load(c, t * BKX_BLOCK + tid, id, &type, &odd);
+        const int npe = bkx_load(c, t * BLOCK + tid, id, &type, &odd);
         if (odd) found |= BK_BAD_ID;
         uint32_t* wt = reinterpret_cast<uint32_t*>(within + t * nb);  // two counts per word (nb is even)
-        for (int i = tid; i < nb / 2; i += BKX_BLOCK) wt[i] = s_h[2 * i] | (s_h[2 * i + 1] << 16);
+        for (int i = tid; i < nb / 2; i += BLOCK) wt[i] = s_h[2 * i] | (s_h[2 * i + 1] << 16);
         __syncthreads();
         const bool crowded = bk_crowded(bk_bucket((uint32_t)id[0], mp.mul));
 #pragma unroll
@@ -104,39 +109,40 @@ __global__ __launch_bounds__(BKX_BLOCK) void bkx_hist_kernel(MixedConn c, BkMap 
         __syncthreads();
     }
     if (found) atomicOr(&s_flags, found);
-    for (int i = tid; i < nb; i += BKX_BLOCK) btot[(int64_t)blockIdx.x * nb + i] = s_h[i];
+    for (int i = tid; i < nb; i += BLOCK) btot[(int64_t)blockIdx.x * nb + i] = s_h[i];
     __syncthreads();
     if (tid == 0) flags[blockIdx.x] = s_flags;
 }
 
-size_t bkx_part_lds(uint32_t nb_pad) {
-    return (size_t)nb_pad * 8 + (size_t)BKX_BLOCK * (MAX_NPE * (4 * BKX_W + 2) + 4 * BKX_IDS);
+size_t bkx_part_lds(int block, uint32_t nb_pad) {
+    return (size_t)nb_pad * 8 + (size_t)block * (MAX_NPE * (4 * BKX_W + 2) + 4 * BKX_IDS);
 }
 
 // As bk_part, a thread per element: its ids go through the LDS, where a
 // position's neighbours are looked up by the element's type.
-__global__ __launch_bounds__(BKX_BLOCK) void bkx_part_kernel(MixedConn c, BkMap mp, int R,
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void bkx_part_kernel(MixedConn c, BkMap mp, int R,
                                                             const uint16_t* __restrict__ within,
                                                             const uint32_t* __restrict__ btot,
                                                             const uint32_t* __restrict__ starts,
                                                             uint32_t* __restrict__ rec, uint32_t* repeats, uint32_t* hdr) {
     extern __shared__ uint32_t s_dyn[];
-    __shared__ uint32_t s_tmp[BKX_BLOCK / WAVE];
+    __shared__ uint32_t s_tmp[BLOCK / WAVE];
     const int nb = (int)mp.nb_pad, tid = threadIdx.x;
     uint32_t* const s_cnt = s_dyn;        // counts, then offsets
     uint32_t* const s_glob = s_dyn + nb;  // where the bucket's first record goes, less its offset
     uint32_t* const s_ids = s_glob + nb + tid * BKX_IDS;
-    uint32_t* const s_rec = s_glob + nb + BKX_BLOCK * BKX_IDS;
-    uint16_t* const s_b = reinterpret_cast<uint16_t*>(s_rec + BKX_BLOCK * MAX_NPE * BKX_W);
+    uint32_t* const s_rec = s_glob + nb + BLOCK * BKX_IDS;
+    uint16_t* const s_b = reinterpret_cast<uint16_t*>(s_rec + BLOCK * MAX_NPE * BKX_W);
     const uint32_t odd = hdr[HDR_BK_ODD];
-    const int64_t t = blockIdx.x, e = t * BKX_BLOCK + tid;
+    const int64_t t = blockIdx.x, e = t * BLOCK + tid;
     const int64_t h = (t / BK_XCDS / R) * BK_XCDS + t % BK_XCDS;
     int32_t id[MAX_NPE];
     uint32_t type;
     bool ill = false;
     bkx_load(c, e, id, &type, &ill);
     const BkxNbr nbr = BKX_NBR[type < N_ELEM_TYPES ? type : 0];
-    for (int i = tid; i < nb; i += BKX_BLOCK) {
+    for (int i = tid; i < nb; i += BLOCK) {
         s_cnt[i] = 0;
         s_glob[i] = i < (int)mp.n_bucket ? starts[i] + btot[h * nb + i] + within[t * nb + i] : 0u;
     }
@@ -151,7 +157,7 @@ __global__ __launch_bounds__(BKX_BLOCK) void bkx_part_kernel(MixedConn c, BkMap 
         const bool ok = v < (uint32_t)mp.n_vert;
         place[j / 2] |= bk_count(s_cnt, ok ? bk_bucket(v, mp.mul) : 0u, ok, crowded) << (16 * (j & 1));
     }
-    const uint32_t total = bk_tile_offsets<BKX_BLOCK>(s_cnt, s_glob, nb, s_tmp);
+    const uint32_t total = bk_tile_offsets<BLOCK>(s_cnt, s_glob, nb, s_tmp);
 #pragma unroll
     for (int j = 0; j < MAX_NPE; ++j) {
         const uint32_t v = (uint32_t)id[j];
@@ -177,7 +183,7 @@ __global__ __launch_bounds__(BKX_BLOCK) void bkx_part_kernel(MixedConn c, BkMap 
         s_b[p] = (uint16_t)b;
     }
     __syncthreads();
-    if (!bk_tile_out<BKX_W, BKX_BLOCK>(s_rec, s_b, s_glob, total, rec, c.n_ids) && !(odd & BK_BAD_ID))
+    if (!bk_tile_out<BKX_W, BLOCK>(s_rec, s_b, s_glob, total, rec, c.n_ids) && !(odd & BK_BAD_ID))
         set_error(hdr + HDR_ERR, ERR_INTERNAL);
 }
 
@@ -187,8 +193,11 @@ void plan_mixed_buckets(int64_t n_elem, int64_t n_ids, int32_t n_vert, const Opt
     *p = BkPlan{};
     // (32-bit sums of up to eight records per element)
     if (!o.library || n_elem > UINT32_MAX / MAX_NPE || !plan_bucket_map(n_elem, n_ids, n_vert, BKX_K, BK_FULL_MIXED, p)) return;
-    if (p->W != BKX_W || bkx_part_lds(p->mp.nb_pad) > (size_t)BK_LDS - 256) return;
-    plan_bucket_layout(BKX_BLOCK, MAX_NPE, limit, p);
+    if (p->W != BKX_W) return;
+    p->large_tile = p->mp.nb_pad > BKX_SMALL_BUCKETS && bkx_part_lds(BKX_LARGE, p->mp.nb_pad) <= (size_t)BK_LDS - 256;
+    const int block = p->large_tile ? BKX_LARGE : BKX_SMALL;
+    if (bkx_part_lds(block, p->mp.nb_pad) > (size_t)BK_LDS - 256) return;
+    plan_bucket_layout(block, MAX_NPE, limit, p);
 }
 
 hipError_t run_mixed_buckets(const BkPlan& p, const int32_t* conn, const int32_t* elem_off, const uint8_t* etypes,
@@ -204,16 +213,21 @@ hipError_t run_mixed_buckets(const BkPlan& p, const int32_t* conn, const int32_t
     uint32_t* starts = (uint32_t*)(w + p.off_starts);
     uint32_t* repeats = (uint32_t*)(w + p.off_rep);
     const int n_scan = (int)ceil_div(p.mp.n_bucket, BKS_COLS);
-    hipError_t e = launch_shm("mixed_bucket_hist", bkx_hist_kernel, dim3(p.hist_blocks), dim3(BKX_BLOCK),
-                              (size_t)p.mp.nb_pad * 4, s, c, p.mp, p.n_tiles, p.R, within, btot, flags, scan_lb, n_scan, hdr);
-    if (e == hipSuccess)
-        e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)n_scan), dim3(BKS_BLOCK), s, btot, p.hist_blocks,
-                   p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags, scan_lb, starts, (uint32_t)p.n_slots,
-                   (uint64_t*)(w + p.off_lb), repeats, hdr);
-    if (e == hipSuccess)
-        e = launch_shm("mixed_bucket_part", bkx_part_kernel, dim3((unsigned)p.n_tiles), dim3(BKX_BLOCK),
-                       bkx_part_lds(p.mp.nb_pad), s, c, p.mp, p.R, (const uint16_t*)within, (const uint32_t*)btot,
-                       (const uint32_t*)starts, (uint32_t*)(w + p.off_rec), repeats, hdr);
+    auto tiles = [&](auto block) {
+        constexpr int BLOCK = decltype(block)::value;
+        hipError_t e = launch_shm("mixed_bucket_hist", bkx_hist_kernel<BLOCK>, dim3(p.hist_blocks), dim3(BLOCK),
+                                  (size_t)p.mp.nb_pad * 4, s, c, p.mp, p.n_tiles, p.R, within, btot, flags, scan_lb, n_scan, hdr);
+        if (e == hipSuccess)
+            e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)n_scan), dim3(BKS_BLOCK), s, btot, p.hist_blocks,
+                       p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags, scan_lb, starts, (uint32_t)p.n_slots,
+                       (uint64_t*)(w + p.off_lb), repeats, hdr);
+        if (e == hipSuccess)
+            e = launch_shm("mixed_bucket_part", bkx_part_kernel<BLOCK>, dim3((unsigned)p.n_tiles), dim3(BLOCK),
+                           bkx_part_lds(BLOCK, p.mp.nb_pad), s, c, p.mp, p.R, (const uint16_t*)within,
+                           (const uint32_t*)btot, (const uint32_t*)starts, (uint32_t*)(w + p.off_rec), repeats, hdr);
+        return e;
+    };
+    const hipError_t e = p.large_tile ? tiles(std::integral_constant<int, BKX_LARGE>{}) : tiles(std::integral_constant<int, BKX_SMALL>{});
     if (e != hipSuccess) return e;
     return launch_bucket_rows(p, node_row_ptr, node_cols, node_cap, elem_row_ptr, elem_cols, elem_cap, w, s);
 }

@@ -56,8 +56,8 @@ bool plan_bucket_map(int64_t n_elem, int64_t n_slots, int32_t n_vert, int K, int
         // a small mesh still spreads over the CUs
         nb = tmax<int64_t>(nb, tmin<int64_t>(BK_CUS, ceil_div(n_slots, BK_LEAST_RECORDS)));
     } else {
-        // two large blocks per CU at a time: whole rounds
-        nb = ceil_div(nb, 2 * BK_CUS) * (2 * BK_CUS);
+        // two large blocks per CU at a time: whole rounds, of equal buckets
+        if (full != BK_FULL_MIXED || nb < 2 * BK_CUS) nb = ceil_div(nb, 2 * BK_CUS) * (2 * BK_CUS);
     }
     const int64_t width = tmax<int64_t>(ceil_div(n_vert, nb), 2);
     m.mul = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)width);
@@ -104,7 +104,7 @@ void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* 
 void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, bool node, size_t limit, BkPlan* p) {
     *p = BkPlan{};
     const int npe = nodes_per_elem(etype);
-    if (!o.library || !plan_bucket_map(n_elem, (int64_t)npe * n_elem, n_vert, node ? bk_neighbours(etype) : 0, BK_FULL, p))
+    if (!o.library || !plan_bucket_map(n_elem, (int64_t)npe * n_elem, n_vert, node ? bk_neighbours(etype) : 0, bk_full(etype), p))
         return;
     p->etype = etype;
     // tiles: large ones once they occupy every CU

@@ -16,11 +16,15 @@ constexpr int BK_SMALL_MOST = 448;
 constexpr int BK_LEAST_RECORDS = 384;  // fewest records a bucket of a small mesh is planned for
 // Records of a bucket, percent of what it holds, on average: a bucket with more
 // than it holds is finished from memory, and every later one waits for it.  The
-// vertices of a mesh of one type differ little; those of a mixed mesh a lot (a
-// cell's centre 0 or 6 elements, a corner 17), and 3 of 512 buckets of 4004
-// records ran over 4480: 204 instead of 83 us for the rows of a hybrid mesh of
-// 2 M ids.
-constexpr int BK_FULL = 92, BK_FULL_MIXED = 80;
+// vertices of most meshes of one type differ little.  A pyramid's apex has 6
+// elements where a corner of its base has 24, and labels with locality put
+// vertices of a kind side by side, so buckets of corners get 24 / 15 of the
+// average; in a hybrid mesh they get about twice the average.  (Local labels, us:
+// element relation of 90^3 pyramid cells 511 at 92 % and 315 at 56 %; hybrid
+// mesh of 4 M ids 472 at 80 % and 203 at 45 %, where shuffled ones take 225 and
+// 228.)
+constexpr int BK_FULL = 92, BK_FULL_PYRAMID = 56, BK_FULL_MIXED = 45;
+constexpr int bk_full(int32_t etype) { return etype == MESH_PYRAMID5 ? BK_FULL_PYRAMID : BK_FULL; }
 constexpr int BK_HIST_BLOCKS = 512;    // blocks of bk_hist aimed at
 
 // Records and vertices a bucket may hold (BkShape).

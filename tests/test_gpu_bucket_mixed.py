@@ -58,8 +58,9 @@ def test_tile_edges(n):
         assert np.array_equal(g, w)
 
 
-def test_large_buckets():
-    m = mg.hybrid_grid(52, seed=4)
+@pytest.mark.parametrize("relabel", [True, False], ids=["shuffled", "kinds_side_by_side"])
+def test_large_buckets_and_tiles(relabel):
+    m = mg.hybrid_grid(52, seed=4, relabel=relabel)
     _check(np.asarray(m.conn).ravel(), np.asarray(m.etypes), m.n_vert, "hybrid")
 
 
