@@ -269,9 +269,9 @@ mesh_status mesh_neighbors_noalloc(const int32_t* conn, int64_t n_elem, int32_t 
  * elem_off int32 [n_elem + 1] with elem_off[0] = 0 and
  * elem_off[e+1] - elem_off[e] = nodes of etypes[e].  n_ids = elem_off[n_elem]
  * (the slot count) and n_pairs = sum of 2 * edges of each element's type are
- * given by the caller for sizing.  Both relations are built; the node
- * relation always takes the ELEM_ROWS algorithm (opts->node_sort must be -1
- * or MESH_NODE_SORT_ELEM_ROWS).  An element whose type code is unknown or
+ * given by the caller for sizing.  Both relations are built, with nothing
+ * named by opts through vertex buckets, else the node relation by the
+ * ELEM_ROWS algorithm (opts->node_sort must be -1 or MESH_NODE_SORT_ELEM_ROWS).  An element whose type code is unknown or
  * whose offsets disagree with its type raises MESH_ERR_INDEX_RANGE on the
  * device and contributes nothing.  Limits: n_ids, n_pairs <= 2^31 - 1. */
 mesh_status mesh_mixed_neighbors_query(int64_t n_elem, int64_t n_ids, int64_t n_pairs, int32_t n_vert,
