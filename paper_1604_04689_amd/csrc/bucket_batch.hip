@@ -457,22 +457,25 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
     p->total_slots = total_slots;
     p->total_pairs = total_pairs;
     p->entries = 2 * (int64_t)n_mesh + 1;
-    int fill_least = INT32_MAX, vmax_least = INT32_MAX;
+    // (records of a bucket of the fullest kind, which decide the bucket size and the most buckets of a mesh, and the
+    // least any is planned for)
+    int full_least = INT32_MAX, fill_least = INT32_MAX, vmax_least = INT32_MAX;
     for (int large = 0; large < 2; ++large) {
         p->large = large != 0;
-        fill_least = vmax_least = INT32_MAX;
+        full_least = fill_least = vmax_least = INT32_MAX;
         for (int K = 2; K <= 4; ++K) {
             const BkSize z = bk_size(K, large != 0);
-            p->fill[K] = z.cap * (K == 4 ? BK_FULL_PYRAMID : BK_FULL) / 100;
             // few records still spread over the CUs
-            if (!large) p->fill[K] = (int32_t)tmin<int64_t>(p->fill[K], tmax<int64_t>(BK_LEAST_RECORDS, total_slots / BK_CUS));
+            const int64_t spread = large ? z.cap : tmax<int64_t>(BK_LEAST_RECORDS, total_slots / BK_CUS);
+            p->fill[K] = (int32_t)tmin<int64_t>(z.cap * (K == 4 ? BK_FULL_PYRAMID : BK_FULL) / 100, spread);
+            full_least = tmin(full_least, (int)tmin<int64_t>(z.cap * BK_FULL / 100, spread));
             fill_least = tmin(fill_least, p->fill[K]);
             vmax_least = tmin(vmax_least, z.vmax - 2);
         }
-        if (ceil_div(total_slots, (int64_t)fill_least) <= BKB_SMALL_MOST) break;
+        if (ceil_div(total_slots, (int64_t)full_least) <= BKB_SMALL_MOST) break;
     }
     const int64_t nb_most = tmax<int64_t>(ceil_div(max_vert, (int64_t)vmax_least),
-                                          ceil_div((int64_t)max_vert * BK_MAX_DEGREE, (int64_t)fill_least)) + 1;
+                                          ceil_div((int64_t)max_vert * BK_MAX_DEGREE, (int64_t)full_least)) + 1;
     if (nb_most > BKB_NB_MOST) return;
     p->nb_most = (int32_t)nb_most;
     // few elements still spread over the CUs
