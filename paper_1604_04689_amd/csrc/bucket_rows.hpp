@@ -740,7 +740,11 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
     // ---- node rows
     uint32_t total = 0;
     if (K > 0 && node) {
-        constexpr uint32_t STUCK = 1u << 24;  // too many distinct values
+        // too many distinct values: more than all rows of a bucket keep (K * CAP is at
+        // most POOL), and small enough that the sum of a whole block of marks and of all
+        // kept values stays below 2^32
+        constexpr uint32_t STUCK = S::POOL + 1;
+        static_assert(K * CAP <= S::POOL && (uint64_t)BLOCK * STUCK + S::POOL <= UINT32_MAX, "marks never cancel out");
         auto rows = [&](auto most) BK_INLINE {  // rounds of up to `most` values
             constexpr int MOST = decltype(most)::value;
             for (int v0 = 0; v0 < nv; v0 += BLOCK) {
@@ -782,7 +786,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
                 // below its own place, so the rows of later rounds are untouched.)
                 const uint32_t off = total + bk_block_sum<BLOCK>(c, s_tmp, turn, &sum);
                 total += sum;
-                if (total >= STUCK) return;
+                if (total >= STUCK) return;  // (before the round stores anything)
                 if (c && (tid & (WAVE - 1)) != spread) bk_row_store<MOST>(x, s_val + off);
                 if (MOST > 16 && spread >= 0) {
                     const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)off, spread);
