@@ -381,11 +381,17 @@ template <int W>
 struct BkWords {
     uint32_t w[W];
 };
-// Record i after rec (a 32-bit byte offset: a bucket's records stay below
-// 2^32 bytes, see the plan).
+// Where record i starts, in bytes.
 template <int W>
+__host__ __device__ constexpr uint64_t bk_record_at(uint64_t i) {
+    return i * (uint64_t)(4 * W);
+}
+static_assert(bk_record_at<5>(1u << 30) == 5ull << 32, "one mesh's records may all be in one bucket, 4 GiB of them and more");
+// Record i after rec.  NEAR: one of a bucket's first CAP, by a 32-bit offset.
+template <int W, bool NEAR = false>
 __device__ __forceinline__ void bk_load(const uint32_t* __restrict__ rec, uint32_t i, uint32_t (&r)[W]) {
-    const BkWords<W> x = *reinterpret_cast<const BkWords<W>*>(reinterpret_cast<const char*>(rec) + i * (uint32_t)(4 * W));
+    const char* at = reinterpret_cast<const char*>(rec);
+    const BkWords<W> x = *reinterpret_cast<const BkWords<W>*>(NEAR ? at + i * (uint32_t)(4 * W) : at + bk_record_at<W>(i));
 #pragma unroll
     for (int q = 0; q < W; ++q) r[q] = x.w[q];
 }
@@ -677,7 +683,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         // (without a branch: past the bucket, its last record again)
-        bk_load<W>(a.rec + rec0 * W, tmin<uint32_t>(q * BLOCK + tid, n ? n - 1 : 0u), r[q]);
+        bk_load<W, true>(a.rec + rec0 * W, tmin<uint32_t>(q * BLOCK + tid, n ? n - 1 : 0u), r[q]);
     }
     for (int v = tid; v < nv; v += BLOCK) {
         s_start[v] = 0;
