@@ -50,21 +50,6 @@ __host__ __device__ inline int32_t bkb_tile_elems(int32_t et, int W, uint32_t nb
     return tmax(1, tmin(tmin(BKB_BLOCK * bkb_ept(et), fit), tile_slots / npe));
 }
 
-// Largest i in [0, n) with off[i] <= x (off ascending from 0), found by a
-// whole wave, 64 places at a time.
-__device__ __forceinline__ int bkb_find(const uint32_t* __restrict__ off, int n, uint32_t x) {
-    const int lane = __lane_id();
-    int lo = 0, len = n;
-    while (len > 1) {
-        const int step = (len + WAVE - 1) / WAVE;
-        const bool ok = lane * step < len && off[lo + lane * step] <= x;
-        const int k = (int)__popcll(__ballot(ok)) - 1;
-        lo += k * step;
-        len = tmin(step, len - k * step);
-    }
-    return __builtin_amdgcn_readfirstlane(lo);
-}
-
 // Inclusive scan over the lanes of a wave (DPP: no LDS round trips); 0 is op's
 // identity.
 template <class Op>
@@ -281,7 +266,7 @@ __global__ __launch_bounds__(BKB_BLOCK) void bkb_hist_kernel(const int32_t* __re
     const uint32_t n_tiles = hdr[HDR_BKB_TILES];
     uint32_t found = 0;
     for (uint32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const int k = bkb_find(tile0, entries, t);
+        const int k = bk_find(tile0, entries, t);
         const BkMesh& m = mesh[k];
         if (tid == 0) tmesh[t] = (uint32_t)k;
         const uint32_t i = t - m.tile0;
@@ -303,22 +288,27 @@ __global__ __launch_bounds__(BKB_BLOCK) void bkb_hist_kernel(const int32_t* __re
 }
 
 // cells: the counts of a mesh's tiles become the records of the bucket in the
-// tiles before, in the order of the tiles' XCDs; totals[b] the bucket's own.  A
+// tiles before, in the order of the tiles' XCDs; totals[b] the bucket's own,
+// more[b] its units less one (bk_shares).  A
 // block takes 16 buckets of one mesh, 16 threads each: 41 us for 512 meshes
 // (30,000 tiles, 24,000 buckets, 26 MB of cells).
 constexpr int BKB_SCAN = 256;
 constexpr int BKB_ROWS = BKB_SCAN / BKS_COLS;
 constexpr int BKB_AHEAD = 8;  // cells read at once
+struct BkbCaps {
+    uint32_t K2, K3, K4;  // records a bucket's block holds
+};
 __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __restrict__ mesh,
                                                            const uint32_t* __restrict__ scan0, int entries,
                                                            uint32_t* __restrict__ cells, uint32_t* __restrict__ totals,
+                                                           uint32_t* __restrict__ more, BkbCaps cap,
                                                            uint32_t* __restrict__ bmesh, uint64_t* __restrict__ lookback,
-                                                           uint32_t* __restrict__ repeats, const uint32_t* hdr) {
+                                                           uint32_t* __restrict__ repeats, uint32_t* hdr) {
     __shared__ uint32_t s_sum[BKB_ROWS][BKS_COLS];
     const int tid = threadIdx.x;
     const uint32_t block = blockIdx.x;
     if (block >= hdr[HDR_BKB_SCANS]) return;
-    const int k = bkb_find(scan0, entries, block);
+    const int k = bk_find(scan0, entries, block);
     const BkMesh& m = mesh[k];
     const int c = tid % BKS_COLS, g = tid / BKS_COLS;
     const uint32_t col = (block - m.scan0) * BKS_COLS + c;
@@ -363,7 +353,11 @@ __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __rest
     }
     if (g == 0 && col < nb) {
         const uint32_t at = m.bucket0 + col;
+        const int K = bkb_K(m.etype);
+        const uint32_t shares = bk_shares(tot, K == 2 ? cap.K2 : K == 3 ? cap.K3 : cap.K4);
         totals[at] = tot;
+        more[at] = shares - 1;
+        if (shares > 1) atomicOr(&hdr[HDR_BKB_SHARED], 1u);
         bmesh[at] = (uint32_t)k;
         lookback[at] = 0;  // bkb_rows'
         repeats[at] = 0;   // counted by bkb_part
@@ -382,9 +376,10 @@ __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __rest
 // sums of bkb_scan's blocks handed on in order, by ticket, both took 170 us: the
 // tickets of 4500 blocks queue at one address.)
 constexpr int BKB_AT_ONCE = 8;
-__global__ __launch_bounds__(BKB_SETUP) void bkb_starts_kernel(uint32_t* __restrict__ starts, const uint32_t* hdr) {
-    __shared__ uint32_t s_w[1][BKB_SETUP_WAVES];
-    const uint32_t n = hdr[HDR_BKB_BUCKETS];
+// a[0 .. n) becomes its exclusive sums, plus its places' numbers with `places`;
+// a[n] the whole.
+__device__ __forceinline__ uint32_t bkb_sums(uint32_t* __restrict__ a, uint32_t n, bool places,
+                                             uint32_t (*s_w)[BKB_SETUP_WAVES]) {
     auto add = [](uint32_t x, uint32_t y) { return x + y; };
     uint32_t carry[1] = {};
     for (uint32_t b0 = 0; b0 < n; b0 += BKB_SETUP * BKB_AT_ONCE) {
@@ -392,17 +387,32 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_starts_kernel(uint32_t* __restr
         uint32_t v[BKB_AT_ONCE], sum[1] = {};
 #pragma unroll
         for (int q = 0; q < BKB_AT_ONCE; ++q) {
-            v[q] = b + q < n ? starts[b + q] : 0u;
+            v[q] = b + q < n ? a[b + q] : 0u;
             sum[0] += v[q];
         }
         bkb_block_scan(sum, carry, s_w, add);
 #pragma unroll
         for (int q = 0; q < BKB_AT_ONCE; ++q) {
-            if (b + q < n) starts[b + q] = sum[0];
+            if (b + q < n) a[b + q] = sum[0] + (places ? b + q : 0u);
             sum[0] += v[q];
         }
     }
-    if (threadIdx.x == 0) starts[n] = carry[0];
+    const uint32_t all = carry[0] + (places ? n : 0u);
+    if (threadIdx.x == 0) a[n] = all;
+    return all;
+}
+__global__ __launch_bounds__(BKB_SETUP) void bkb_starts_kernel(uint32_t* __restrict__ starts, uint32_t* __restrict__ units,
+                                                              uint64_t* __restrict__ lookback, uint32_t* hdr) {
+    __shared__ uint32_t s_w[1][BKB_SETUP_WAVES];
+    const uint32_t n = hdr[HDR_BKB_BUCKETS];
+    const bool shared = hdr[HDR_BKB_SHARED] != 0;
+    bkb_sums(starts, n, false, s_w);
+    uint32_t all = n;
+    if (shared) {
+        all = bkb_sums(units, n, true, s_w);
+        for (uint32_t u = n + threadIdx.x; u < all; u += BKB_SETUP) lookback[u] = 0;
+    }
+    if (threadIdx.x == 0) hdr[HDR_BK_UNITS] = all;
 }
 
 // Two tiles per CU at a time.  Bound by the records' way out: the 137 M slots
@@ -486,6 +496,9 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
                                                    bkb_tile_elems(et, bkb_K(et) + 1, (uint32_t)nb_most + 1, p->tile_slots));
     const int64_t n = p->entries;
     p->bucket_most = ceil_div(total_slots, (int64_t)fill_least) + ceil_div(total_vert, (int64_t)vmax_least) + 3 * n;
+    p->unit_most = p->bucket_most;
+    for (int K = 2; K <= 4; ++K)
+        p->unit_most = tmax(p->unit_most, bk_unit_most(p->bucket_most, total_slots, bk_size(K, p->large).cap));
     p->tile_most = ceil_div(total_slots, tile_least) + n;
     p->scan_most = ceil_div(p->bucket_most, (int64_t)BKS_COLS) + n;
     p->cell_most = p->tile_most * (nb_most + 1);
@@ -502,8 +515,9 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
     take(&p->off_bmesh, (size_t)p->bucket_most * 4);
     take(&p->off_tmesh, (size_t)p->tile_most * 4);
     take(&p->off_starts, ((size_t)p->bucket_most + 1) * 4);
+    take(&p->off_units, ((size_t)p->bucket_most + 1) * 4);
     take(&p->off_rep, (size_t)p->bucket_most * 4);
-    take(&p->off_lb, (size_t)p->bucket_most * 8);
+    take(&p->off_lb, (size_t)p->unit_most * 8);
     take(&p->off_cells, (size_t)p->cell_most * 4);
     take(&p->off_rec, (size_t)p->word_most * 4);
     p->total = off;
@@ -538,7 +552,10 @@ hipError_t run_batch_buckets(const BkBatchPlan& p, const int32_t* conn, const me
     uint32_t* tmesh = (uint32_t*)(w + p.off_tmesh);
     uint32_t* cells = (uint32_t*)(w + p.off_cells);
     uint32_t* starts = (uint32_t*)(w + p.off_starts);
+    uint32_t* units = (uint32_t*)(w + p.off_units);
     uint32_t* repeats = (uint32_t*)(w + p.off_rep);
+    uint64_t* lookback = (uint64_t*)(w + p.off_lb);
+    const BkbCaps caps{(uint32_t)bk_size(2, p.large).cap, (uint32_t)bk_size(3, p.large).cap, (uint32_t)bk_size(4, p.large).cap};
     const auto grid = [&](int64_t per_cu) {  // a multiple of the XCDs
         return dim3((unsigned)tmin<int64_t>(ceil_div(p.tile_most, (int64_t)BK_XCDS) * BK_XCDS, per_cu * BK_CUS));
     };
@@ -548,10 +565,10 @@ hipError_t run_batch_buckets(const BkBatchPlan& p, const int32_t* conn, const me
                        mesh, (const uint32_t*)a.tile0, entries, tmesh, cells, hdr);
     if (e == hipSuccess)
         e = launch("batch_bucket_scan", bkb_scan_kernel, dim3((unsigned)p.scan_most), dim3(BKB_SCAN), s, mesh,
-                   (const uint32_t*)a.scan0, entries, cells, starts, (uint32_t*)(w + p.off_bmesh),
-                   (uint64_t*)(w + p.off_lb), repeats, (const uint32_t*)hdr);
+                   (const uint32_t*)a.scan0, entries, cells, starts, units, caps, (uint32_t*)(w + p.off_bmesh), lookback,
+                   repeats, hdr);
     if (e == hipSuccess)
-        e = launch("batch_bucket_starts", bkb_starts_kernel, dim3(1), dim3(BKB_SETUP), s, starts, (const uint32_t*)hdr);
+        e = launch("batch_bucket_starts", bkb_starts_kernel, dim3(1), dim3(BKB_SETUP), s, starts, units, lookback, hdr);
     if (e == hipSuccess)
         e = launch_shm("batch_bucket_part", bkb_part_kernel, grid(2), dim3(BKB_BLOCK), (size_t)BKB_LDS, s, conn, mesh,
                        (const uint32_t*)tmesh, (const uint32_t*)cells, (const uint32_t*)starts,

@@ -7,6 +7,7 @@ namespace mnb {
 
 // Header words (HDR_*) that hold what the device found the batch to need.
 constexpr int HDR_BKB_BUCKETS = 48, HDR_BKB_TILES = 49, HDR_BKB_SCANS = 50;
+constexpr int HDR_BKB_SHARED = 51;  // some bucket has shares
 
 // One entry of the batch's bucket table: a mesh, or the vertices between two
 // meshes' ranges that no valid record covers (usually none).
@@ -29,9 +30,9 @@ struct BkBatchPlan {
     int32_t fill[5] = {};    // records a bucket is planned for, by K
     int32_t nb_most = 0;     // most buckets of one mesh
     int32_t tile_slots = 0;  // most slots per tile
-    int64_t entries = 0, bucket_most = 0, tile_most = 0, scan_most = 0, cell_most = 0, word_most = 0;
+    int64_t entries = 0, bucket_most = 0, unit_most = 0, tile_most = 0, scan_most = 0, cell_most = 0, word_most = 0;
     size_t off_mesh = 0, off_tile0 = 0, off_scan0 = 0, off_bmesh = 0, off_tmesh = 0, off_starts = 0,
-           off_rep = 0, off_lb = 0, off_cells = 0, off_rec = 0;
+           off_units = 0, off_rep = 0, off_lb = 0, off_cells = 0, off_rec = 0;
     size_t total = 0;
 };
 

@@ -23,11 +23,12 @@
 // its element rows, so that the answer is usually there when it asks.
 //
 // What the registers do not take is done from the records in memory again
-// (bk_node_ranges, bk_elem_ranges): a bucket with more records than the LDS
-// holds, which an uneven mesh has, in several ranges of its vertices, first to
-// count and then to write; one with a row of more than 64 distinct neighbours
-// in one; a single row longer than the LDS in bit maps of a window of ids at a
-// time.
+// (bk_ranges): a bucket with a row of more than 64 distinct neighbours, and one
+// with more records than the LDS holds, which an uneven mesh has.  Several
+// blocks share the latter: each has its own place in the look-back and takes a
+// run of the bucket's vertices, in ranges that fit the LDS, first to count and
+// then to write; a single row longer than the LDS is done in bit maps of a
+// window of ids at a time, the windows dealt to the shares that the row spans.
 #pragma once
 
 #include <utility>
@@ -39,6 +40,14 @@ namespace mnb {
 // Lambdas that see register arrays go in before anything else is optimised:
 // code shared by two of them would otherwise be merged through memory.
 #define BK_INLINE __attribute__((always_inline))
+
+// The thread's number in its block, afresh: what follows from it is not kept
+// from one unit of a block for the next, in registers that the rows need.
+__device__ __forceinline__ int bk_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 
 // ---- sorting -----------------------------------------------------------------
 // Batcher's odd-even merge sort of N values, any N: its comparators in order.
@@ -166,7 +175,7 @@ __device__ __forceinline__ void bk_wave_sync() {
 // values where the same in LDS took 10 (a round trip per step).
 template <int E>
 __device__ __forceinline__ uint32_t bk_wave_sort_unique(uint32_t* a, uint32_t n) {
-    const uint32_t lane = __lane_id();
+    const uint32_t lane = (uint32_t)(bk_tid() & (WAVE - 1));
     uint32_t x[E];
     bk_each<E>([&](auto rr) BK_INLINE {
         constexpr int r = decltype(rr)::value;
@@ -216,7 +225,7 @@ __device__ __forceinline__ uint32_t bk_wave_sort_unique(uint32_t* a, uint32_t n)
 // every lane of that wave.
 template <bool BLOCKWIDE, int THREADS>
 __device__ inline uint32_t bk_lds_sort_unique(uint32_t* a, uint32_t n) {
-    const uint32_t me = BLOCKWIDE ? threadIdx.x : (uint32_t)__lane_id();
+    const uint32_t me = BLOCKWIDE ? (uint32_t)bk_tid() : (uint32_t)(bk_tid() & (WAVE - 1));
     auto sync = [] {
         if constexpr (BLOCKWIDE) __syncthreads();
         else bk_wave_sync();
@@ -240,8 +249,8 @@ __device__ inline uint32_t bk_lds_sort_unique(uint32_t* a, uint32_t n) {
         }
     }
     uint32_t cnt = 0;
-    if (!BLOCKWIDE || threadIdx.x < WAVE) {
-        const uint32_t lane = __lane_id();
+    if (!BLOCKWIDE || bk_tid() < WAVE) {
+        const uint32_t lane = (uint32_t)(bk_tid() & (WAVE - 1));
         const uint64_t lt = (1ull << lane) - 1;
         uint32_t prev = BK_EMPTY;
         for (uint32_t c0 = 0; c0 < n; c0 += WAVE) {
@@ -276,6 +285,7 @@ struct BkRowsArgs {
     BkMap mp;
     const uint32_t* rec;
     const uint32_t* starts;
+    const uint32_t* units;    // first unit per bucket
     const uint32_t* repeats;  // per bucket: records whose pair an earlier record of the element has
     uint64_t* lookback;
     uint32_t* hdr;
@@ -331,11 +341,11 @@ __device__ __forceinline__ uint32_t bk_wave_sum(uint32_t x) {
 template <int BLOCK>
 __device__ __forceinline__ uint32_t bk_block_sum(uint32_t v, uint32_t* s_tmp, int* turn, uint32_t* total) {
     constexpr int WAVES = BLOCK / WAVE;
-    const int wid = threadIdx.x / WAVE;
+    const int wid = bk_tid() / WAVE;
     uint32_t* t = s_tmp + *turn * WAVES;
     *turn ^= 1;
     const uint32_t incl = bk_wave_sum(v);
-    if ((threadIdx.x & (WAVE - 1)) == WAVE - 1) t[wid] = incl;
+    if ((bk_tid() & (WAVE - 1)) == WAVE - 1) t[wid] = incl;
     __syncthreads();
     uint32_t before = 0, sum = 0;
 #pragma unroll
@@ -354,7 +364,7 @@ template <int BLOCK, int MAXN>
 __device__ __forceinline__ uint32_t bk_scan_lds(uint32_t* s, int n, uint32_t* s_tmp, int* turn) {
     constexpr int PER = (MAXN + BLOCK - 1) / BLOCK;
     uint32_t v[PER], sum = 0;
-    const int i0 = (int)threadIdx.x * PER;
+    const int i0 = bk_tid() * PER;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         v[q] = i0 + q < n ? s[i0 + q] : 0u;
@@ -367,15 +377,28 @@ __device__ __forceinline__ uint32_t bk_scan_lds(uint32_t* s, int n, uint32_t* s_
         if (i0 + q < n) s[i0 + q] = run;
         run += v[q];
     }
-    if (threadIdx.x == 0) s[n] = total;
+    if (bk_tid() == 0) s[n] = total;
     __syncthreads();
     return total;
 }
 
-// Barrier and a vote of the block, as a scalar: a branch on it is uniform for
-// the compiler too, so what one side keeps in registers does not live through
-// the other.
-__device__ __forceinline__ bool bk_any(bool x) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(x)) != 0; }
+// Barrier and a vote of the block (s_tmp and turn as in bk_block_sum), as a
+// scalar: a branch on it is uniform for the compiler too, so what one side keeps
+// in registers does not live through the other.
+template <int BLOCK>
+__device__ __forceinline__ bool bk_any(bool x, uint32_t* s_tmp, int* turn) {
+    constexpr int WAVES = BLOCK / WAVE;
+    const int tid = bk_tid();
+    uint32_t* t = s_tmp + *turn * WAVES;
+    *turn ^= 1;
+    const bool any = __ballot(x) != 0;
+    if ((tid & (WAVE - 1)) == 0) t[tid / WAVE] = any ? 1u : 0u;
+    __syncthreads();
+    uint32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) all |= t[w];
+    return __builtin_amdgcn_readfirstlane((int)all) != 0;
+}
 
 template <int W>
 struct BkWords {
@@ -387,7 +410,7 @@ __host__ __device__ constexpr uint64_t bk_record_at(uint64_t i) {
     return i * (uint64_t)(4 * W);
 }
 static_assert(bk_record_at<5>(1u << 30) == 5ull << 32, "one mesh's records may all be in one bucket, 4 GiB of them and more");
-// Record i after rec.  NEAR: one of a bucket's first CAP, by a 32-bit offset.
+// Record i after rec.  NEAR: one of the first few, by a 32-bit offset.
 template <int W, bool NEAR = false>
 __device__ __forceinline__ void bk_load(const uint32_t* __restrict__ rec, uint32_t i, uint32_t (&r)[W]) {
     const char* at = reinterpret_cast<const char*>(rec);
@@ -396,18 +419,48 @@ __device__ __forceinline__ void bk_load(const uint32_t* __restrict__ rec, uint32
     for (int q = 0; q < W; ++q) r[q] = x.w[q];
 }
 
-// The bucket's node entries go to the look-back word, the sum of the earlier
-// buckets' comes back (every thread).
-__device__ __forceinline__ void bk_publish(const BkRowsArgs& a, uint32_t bucket, uint64_t mine) {
-    if (threadIdx.x == 0) lb_store(a.lookback + bucket, (bucket == 0 ? LB_INC : LB_AGG) | mine);
+// What a block does: a bucket, or one of the shares of one.  Its unit is its
+// place in the look-back, in the order of the rows.
+struct BkUnit {
+    uint32_t unit, bucket, share, shares;
+    bool last;  // of all
+};
+// The unit's node entries go to the look-back word, the sum of the earlier
+// units' comes back (every thread).
+__device__ __forceinline__ void bk_publish(const BkRowsArgs& a, uint32_t unit, uint64_t mine) {
+    if (bk_tid() == 0) lb_store(a.lookback + unit, (unit == 0 ? LB_INC : LB_AGG) | mine);
 }
-__device__ __forceinline__ uint64_t bk_before(const BkRowsArgs& a, uint32_t bucket, uint64_t mine, uint64_t* s_base) {
-    if (threadIdx.x < WAVE) {
-        const uint64_t p = wave_lookback_prefix(a.lookback, bucket, mine, a.hdr + HDR_ERR);
-        if (threadIdx.x == 0) *s_base = p;
+__device__ __forceinline__ uint64_t bk_before(const BkRowsArgs& a, uint32_t unit, uint64_t mine, uint64_t* s_base) {
+    if (bk_tid() < WAVE) {
+        const uint64_t p = wave_lookback_prefix(a.lookback, unit, mine, a.hdr + HDR_ERR, a.hdr + HDR_BK_PROGRESS);
+        if (bk_tid() == 0) *s_base = p;
     }
     __syncthreads();
     return *s_base;
+}
+
+// f(record) for the n records at rec, over the block, BK_AHEAD of a thread's
+// loads on their way at once.  Counts as a step for those that wait.
+constexpr int BK_AHEAD = 8;
+constexpr uint32_t BK_STEP = 1u << 20;  // records of a step
+template <int W, int BLOCK, class F>
+__device__ __forceinline__ void bk_each_record(const BkRowsArgs& a, const uint32_t* rec, uint32_t n, F&& f) {
+    for (uint32_t c0 = 0; c0 < n; c0 += BK_STEP) {
+        if (bk_tid() == 0) atomicAdd(a.hdr + HDR_BK_PROGRESS, 1u);
+        const uint32_t m = tmin(n - c0, BK_STEP);
+        const uint32_t* at = rec + bk_record_at<W>(c0) / 4;
+        for (uint32_t i0 = (uint32_t)bk_tid(); i0 < m; i0 += BK_AHEAD * BLOCK) {
+            uint32_t r[BK_AHEAD][W];
+            bk_each<BK_AHEAD>([&](auto uu) BK_INLINE {
+                constexpr int u = decltype(uu)::value;
+                bk_load<W, true>(at, tmin(i0 + u * BLOCK, m - 1), r[u]);
+            });
+            bk_each<BK_AHEAD>([&](auto uu) BK_INLINE {
+                constexpr int u = decltype(uu)::value;
+                if (i0 + u * BLOCK < m) f(r[u]);
+            });
+        }
+    }
 }
 
 // Values [src, src + left) of a row, in windows of up to MOST values at a time,
@@ -447,7 +500,7 @@ template <int BLOCK>
 __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s_start, uint32_t s0, int va, int vb,
                                               uint32_t per, uint32_t* s_cnt, uint16_t* s_pos) {
     constexpr uint32_t LONG = 1u << 31, DONE = 1u << 30, WAVE_MAX = 1024;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid / WAVE;
+    const int tid = bk_tid(), lane = tid & (WAVE - 1), wid = tid / WAVE;
     __syncthreads();
     for (int v0 = va + wid * WAVE; v0 < vb; v0 += BLOCK) {
         const int v = v0 + lane;
@@ -490,30 +543,30 @@ __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s
     }
 }
 
-// One row (vertex v of the bucket) beyond the LDS: its ids below `range` in
-// bit maps of `words` words at s_map.  With write, they go to cols from `at`
-// on (as far as cap lets).  Returns their number.
+// Windows [wa, wb) of one row (vertex v of the bucket) beyond the LDS, each its
+// ids in a bit map of `words` words at s_map.  With write, they go to cols from
+// `at` on (as far as cap lets); for elements, which have no repeats where wa >
+// 0, `at` is where the whole row starts.  Returns their number.
 template <int K, int W, int BLOCK>
 __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint32_t* rec, uint32_t n, uint32_t lo, int v,
-                                                bool elements, uint32_t* s_map, uint32_t words, uint32_t* s_tmp,
-                                                int* turn, bool write, int32_t* cols, uint64_t at, int64_t cap,
-                                                bool* full) {
-    const int tid = threadIdx.x;
+                                                uint32_t wa, uint32_t wb, bool elements, uint32_t* s_map, uint32_t words,
+                                                uint32_t* s_tmp, int* turn, bool write, int32_t* cols, uint64_t at,
+                                                int64_t cap, bool* full) {
+    const int tid = bk_tid();
     const uint32_t per = (words + BLOCK - 1) / BLOCK;
-    const uint64_t range = elements ? (uint64_t)a.n_elem : (uint64_t)a.mp.n_vert;
     uint32_t all = 0;
-    for (uint64_t w0 = 0; w0 < range; w0 += 32ull * words) {
+    for (uint32_t w = wa; w < wb; ++w) {
+        const uint32_t w0 = w * 32 * words;  // (below 2^31: an id)
+        uint32_t below = 0;
         __syncthreads();
         for (uint32_t i = tid; i < words; i += BLOCK) s_map[i] = 0;
         __syncthreads();
-#pragma unroll 4
-        for (uint32_t i = tid; i < n; i += BLOCK) {
-            uint32_t r[W];
-            bk_load<W>(rec, i, r);
-            if (bk_row<K, W>(a.mp, r, lo) != (uint32_t)v) continue;
+        bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
+            if (bk_row<K, W>(a.mp, r, lo) != (uint32_t)v) return;
             auto put = [&](uint32_t x) BK_INLINE {
-                const uint64_t o = (uint64_t)x - w0;
-                if (x >= w0 && o < 32ull * words) atomicOr(&s_map[o >> 5], 1u << (o & 31));
+                const uint32_t o = x - w0;
+                if (x < w0) ++below;
+                else if (o < 32 * words) atomicOr(&s_map[o >> 5], 1u << (o & 31));
             };
             if (elements) {
                 put(bk_elem<K, W>(a.mp, r));
@@ -524,16 +577,18 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
                     if (x != lo + (uint32_t)v) put(x);
                 }
             }
-        }
+        });
         __syncthreads();
         uint32_t c = 0;
         for (uint32_t i = tid * per; i < tmin<uint32_t>((tid + 1) * per, words); ++i) c += (uint32_t)__popc(s_map[i]);
-        uint32_t total;
+        uint32_t total, skip = 0;
+        if (elements && w == wa && wa > 0) bk_block_sum<BLOCK>(below, s_tmp, turn, &skip);
+        at += skip;
         uint64_t d = at + all + bk_block_sum<BLOCK>(c, s_tmp, turn, &total);
         if (write)
             for (uint32_t i = tid * per; i < tmin<uint32_t>((tid + 1) * per, words); ++i)
                 for (uint32_t m = s_map[i]; m; m &= m - 1, ++d) {
-                    if ((int64_t)d < cap) cols[d] = (int32_t)(w0 + 32ull * i + __builtin_ctz(m));
+                    if ((int64_t)d < cap) cols[d] = (int32_t)(w0 + 32 * i + __builtin_ctz(m));
                     else *full = true;
                 }
         all += total;
@@ -546,17 +601,14 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
 template <int K, int W, int BLOCK, int VMAX>
 __device__ __forceinline__ void bk_count_records(const BkRowsArgs& a, const uint32_t* rec, uint32_t n, uint32_t lo, int nv,
                                                  uint32_t* s_start, uint32_t* s_tmp, int* turn) {
-    const int tid = threadIdx.x;
+    const int tid = bk_tid();
     __syncthreads();
     for (int v = tid; v < nv; v += BLOCK) s_start[v] = 0;
     __syncthreads();
-#pragma unroll 4
-    for (uint32_t i = tid; i < n; i += BLOCK) {
-        uint32_t r[W];
-        bk_load<W>(rec, i, r);
+    bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
         const uint32_t v = bk_row<K, W>(a.mp, r, lo);
         if (v < (uint32_t)nv) atomicAdd(&s_start[v], 1u);
-    }
+    });
     __syncthreads();
     bk_scan_lds<BLOCK, VMAX>(s_start, nv, s_tmp, turn);
 }
@@ -570,21 +622,32 @@ __device__ __forceinline__ int bk_range_end(const uint32_t* s_start, int va, int
     return __builtin_amdgcn_readfirstlane(vb);
 }
 
-// One relation of any bucket, from its records in memory: ranges of vertices
-// whose records fit the LDS.  elements: the element rows, which start at
-// `ebase`; else the node rows, which are counted first (a bucket in one range
-// keeps them in the LDS meanwhile).  Every thread of the block calls it.
+// The first vertex whose records start at x or beyond (nv: none).
+__device__ __forceinline__ int bk_first_from(const uint32_t* s_start, int nv, uint32_t x) {
+    int v = 0;
+    for (int step = 4096; step >= 1; step >>= 1)
+        if (v + step <= nv && s_start[v + step - 1] < x) v += step;
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// One relation of any unit, from its bucket's records in memory: ranges of
+// vertices whose records fit the LDS.  elements: the element rows, the bucket's
+// starting at `ebase`; else the node rows, which are counted first (a unit in
+// one range keeps them in the LDS meanwhile).  Share i takes the vertices whose
+// records start in the i-th part of the bucket's.  Every thread of the block
+// calls it.
 template <int K, int W, bool LARGE>
-__device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, uint32_t bucket, int64_t rec0, uint32_t n,
+__device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, BkUnit u, int64_t rec0, uint32_t n,
                                           uint32_t lo, int nv, uint64_t ebase, uint32_t* s_val, uint32_t* s_start,
                                           uint32_t* s_cnt, uint16_t* s_pos, uint32_t* s_tmp, int* turn,
                                           uint64_t* s_base) {
     using S = BkShape<K, LARGE>;
     constexpr int BLOCK = S::BLOCK;
+    constexpr uint32_t WINDOW = 32u * S::POOL;  // ids of a bit map
     // (nothing of this rarely taken path is computed ahead of it, where it would
     // cost the other path registers)
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid), "+s"(n), "+s"(lo), "+s"(nv));
+    const int tid = bk_tid();
+    asm volatile("" : "+s"(n), "+s"(lo), "+s"(nv));
     const int lane = tid & (WAVE - 1), wid = tid / WAVE;
     const uint32_t* rec = a.rec + rec0 * W;
     const uint32_t per = elements ? 1u : (uint32_t)(K > 0 ? K : 1);
@@ -592,32 +655,47 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, ui
     int32_t* const rp = elements ? a.erp : a.nrp;
     int32_t* const cols = elements ? a.ecols : a.ncols;
     const int64_t cap = elements ? a.ecap : a.ncap;
+    const uint32_t windows = (uint32_t)(((elements ? (uint64_t)a.n_elem : (uint64_t)a.mp.n_vert) + WINDOW - 1) / WINDOW);
     bool full = false;
     bk_count_records<K, W, BLOCK, S::VMAX>(a, rec, n, lo, nv, s_start, s_tmp, turn);
-    const bool single = bk_range_end(s_start, 0, nv, most) == nv;
+    int v0 = 0, v1 = nv;
+    bool head = false;  // the share starts inside the row of vertex v0 - 1, beyond the LDS
+    const uint32_t part = (n + u.shares - 1) / u.shares;
+    if (u.shares > 1) {
+        v0 = u.share == 0 ? 0 : bk_first_from(s_start, nv, u.share * part);
+        if (u.share + 1 < u.shares) v1 = bk_first_from(s_start, nv, (u.share + 1) * part);
+        head = v0 > 0 && s_start[v0] > u.share * part && s_start[v0] - s_start[v0 - 1] > most;
+    }
+    // the windows of long row v that share u takes: the row spans shares first .. end - 1
+    auto window = [&](int v, bool end) BK_INLINE {
+        if (u.shares == 1) return end ? windows : 0u;
+        const uint32_t first = s_start[v] / part, shares = (s_start[v + 1] - 1) / part + 1 - first;
+        return (uint32_t)((uint64_t)windows * (u.share - first + (end ? 1 : 0)) / shares);
+    };
+    const bool single = !head && (v0 == v1 || bk_range_end(s_start, v0, v1, most) == v1);
     uint64_t base = ebase, run = 0;
+    if (elements) base += s_start[head ? v0 - 1 : v0];
+    else base = 0;
     for (int phase = elements ? 1 : 0; phase < 2; ++phase) {  // 0: count, 1: write
         run = 0;
-        for (int va = 0; va < nv;) {
-            const int vb = bk_range_end(s_start, va, nv, most);
+        for (int va = head ? v0 - 1 : v0; va < v1;) {
+            const int vb = va < v0 ? va : bk_range_end(s_start, va, v1, most);
             const uint64_t at = base + run;
             if (vb == va) {
-                if (phase == 1 && tid == 0) rp[lo + va] = (int32_t)at;
-                run += bk_huge_row<K, W, BLOCK>(a, rec, n, lo, va, elements, s_val, (uint32_t)S::POOL, s_tmp, turn,
-                                                phase == 1, cols, at, cap, &full);
+                if (phase == 1 && va >= v0 && tid == 0) rp[lo + va] = (int32_t)at;
+                run += bk_huge_row<K, W, BLOCK>(a, rec, n, lo, va, window(va, false), window(va, true), elements, s_val,
+                                                (uint32_t)S::POOL, s_tmp, turn, phase == 1, cols, at, cap, &full);
                 ++va;
+                if (elements && u.shares > 1) run = ebase + s_start[va] - base;  // (its end, if here; else nothing follows)
                 continue;
             }
             const uint32_t s0 = s_start[va];
             if (phase == 0 || elements || !single) {
                 for (int v = va + tid; v < vb; v += BLOCK) s_cnt[v] = 0;
                 __syncthreads();
-#pragma unroll 4
-                for (uint32_t i = tid; i < n; i += BLOCK) {
-                    uint32_t r[W];
-                    bk_load<W>(rec, i, r);
+                bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
                     const uint32_t v = bk_row<K, W>(a.mp, r, lo);
-                    if (v < (uint32_t)va || v >= (uint32_t)vb) continue;
+                    if (v < (uint32_t)va || v >= (uint32_t)vb) return;
                     const uint32_t slot = s_start[v] - s0 + atomicAdd(&s_cnt[v], 1u);
                     if (elements) {
                         s_val[slot] = bk_elem<K, W>(a.mp, r);
@@ -628,7 +706,7 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, ui
                             s_val[slot * K + k] = x == lo + v ? BK_EMPTY : x;
                         }
                     }
-                }
+                });
                 bk_sort_range<BLOCK>(s_val, s_start, s0, va, vb, per, s_cnt, s_pos);
                 __syncthreads();
                 bk_scan_lds<BLOCK, S::VMAX>(s_cnt + va, vb - va, s_tmp, turn);
@@ -649,12 +727,12 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, ui
             va = vb;
         }
         if (phase == 0) {
-            bk_publish(a, bucket, run);
-            base = bk_before(a, bucket, run, s_base);
+            bk_publish(a, u.unit, run);
+            base = bk_before(a, u.unit, run, s_base);
             __syncthreads();
         }
     }
-    if (bucket + 1 == a.mp.n_bucket && tid == 0) rp[a.mp.n_vert] = (int32_t)(base + run);
+    if (u.last && tid == 0) rp[a.mp.n_vert] = (int32_t)(base + run);
     if (full) set_error(a.hdr + HDR_ERR, ERR_CAPACITY);
 }
 
@@ -665,7 +743,7 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, ui
 // than 32 among 64 rows), or no room for the elements beside the node rows
 // (rows without repeats).
 template <int K, int W, bool LARGE>
-__device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket, int64_t rec0, uint32_t n, uint32_t lo,
+__device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u, int64_t rec0, uint32_t n, uint32_t lo,
                                             int nv, uint32_t odd, bool elem, uint64_t ebase, uint32_t* s_val,
                                             uint32_t* s_start,
                                             uint32_t* s_cnt, uint32_t* s_tmp, int* turn, uint64_t* s_base) {
@@ -674,9 +752,8 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
     constexpr int R = (CAP + BLOCK - 1) / BLOCK;  // records per thread
     constexpr uint32_t NONE = 0xffffffffu, NO_SLOT = 0xffffu;
     static_assert(CAP < (int)NO_SLOT, "16-bit slots");
-    const int tid = threadIdx.x;
+    const int tid = bk_tid();
     const bool node = K > 0 && a.nrp != nullptr;
-    const bool last = bucket + 1 == a.mp.n_bucket;
 
     // ---- records into registers; counters and tables cleared meanwhile
     uint32_t r[R][W];
@@ -739,7 +816,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
     bool wide = false;  // some node row needs more than the 16-wide network
     if (K > 0 && node) {
         for (int v = tid; v < nv; v += BLOCK) wide |= K * deg(v) > 16;
-        wide = bk_any(wide);
+        wide = bk_any<BLOCK>(wide, s_tmp, turn);
     }
     __syncthreads();
 
@@ -805,7 +882,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
         else rows(std::integral_constant<int, 16>{});
         // a row beyond the networks, or no room for the elements after the packed rows
         if (total + n > (uint32_t)S::POOL) return false;
-        bk_publish(a, bucket, total);
+        bk_publish(a, u.unit, total);
     }
 
     // ---- element rows, while the look-back word is on its way
@@ -838,7 +915,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
                 });
             });
         }
-        if (bk_any(lng)) {  // longer rows: a wave each up to 1024 elements, the block beyond
+        if (bk_any<BLOCK>(lng, s_tmp, turn)) {  // longer rows: a wave each up to 1024 elements, the block beyond
             for (int v0 = 0; v0 < nv; v0 += WAVE) {
                 const int v = v0 + (tid & (WAVE - 1));
                 const uint32_t d = v < nv ? deg(v) : 0u;
@@ -855,7 +932,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
             __syncthreads();
         }
         for (int v = tid; v < nv; v += BLOCK) a.erp[lo + v] = (int32_t)(ebase + s_start[v]);
-        if (last && tid == 0) a.erp[a.mp.n_vert] = (int32_t)(ebase + n);
+        if (u.last && tid == 0) a.erp[a.mp.n_vert] = (int32_t)(ebase + n);
         if ((int64_t)(ebase + n) > a.ecap) full = true;
         else
             for (uint32_t i = tid; i < n; i += BLOCK) a.ecols[ebase + i] = (int32_t)s_elem[i];
@@ -863,9 +940,9 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
 
     // ---- node rows out
     if (K > 0 && node) {
-        const uint64_t base = bk_before(a, bucket, total, s_base);
+        const uint64_t base = bk_before(a, u.unit, total, s_base);
         for (int v = tid; v < nv; v += BLOCK) a.nrp[lo + v] = (int32_t)(base + s_cnt[v]);
-        if (last && tid == 0) a.nrp[a.mp.n_vert] = (int32_t)(base + total);
+        if (u.last && tid == 0) a.nrp[a.mp.n_vert] = (int32_t)(base + total);
         if ((int64_t)(base + total) > a.ncap) full = true;
         else
             for (uint32_t i = tid; i < total; i += BLOCK) a.ncols[base + i] = (int32_t)s_val[i];
@@ -876,19 +953,19 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, uint32_t bucket
     return true;
 }
 
-// Bucket `bucket` (n records from rec0 on, the r0-th pair of all): both its
+// Unit u, of a bucket of n records from rec0 on, the r0-th pair of all: both its
 // relations.  Every thread of the block calls it.
 template <int K, int W, bool LARGE>
-__device__ __forceinline__ void bk_bucket_rows(const BkRowsArgs& a, uint32_t bucket, int64_t rec0, uint32_t n,
-                                               uint32_t r0, uint32_t lo, int nv, uint32_t odd, uint32_t* s_all,
-                                               uint32_t* s_tmp, uint64_t* s_base) {
+__device__ __forceinline__ void bk_unit_rows(const BkRowsArgs& a, const BkUnit& u, int64_t rec0, uint32_t n, uint32_t r0,
+                                             uint32_t lo, int nv, uint32_t odd, uint32_t* s_all, uint32_t* s_tmp,
+                                             uint64_t* s_base) {
     using S = BkShape<K, LARGE>;
     using L = BkLds<K, LARGE>;
     uint32_t* const s_val = s_all;
     uint32_t* const s_start = s_val + L::VAL;       // row starts
     uint32_t* const s_cnt = s_start + S::VMAX + 1;  // distinct neighbours, then their offsets
     uint16_t* const s_pos = reinterpret_cast<uint16_t*>(s_cnt + S::VMAX + 1);  // bk_ranges
-    const int tid = threadIdx.x;
+    const int tid = bk_tid();
     if (nv < 0 || nv > S::VMAX) {  // never: the plan keeps a bucket's vertices below VMAX
         if (tid == 0) set_error(a.hdr + HDR_ERR, ERR_INTERNAL);
         return;
@@ -900,21 +977,37 @@ __device__ __forceinline__ void bk_bucket_rows(const BkRowsArgs& a, uint32_t buc
     bool repeats = false;
     if (odd & BK_HAS_DUP) {
         uint32_t sum = 0, total;
-        for (uint32_t b = tid; b < bucket; b += S::BLOCK) sum += a.repeats[b];
+        for (uint32_t b = tid; b < u.bucket; b += S::BLOCK) sum += a.repeats[b];
         bk_block_sum<S::BLOCK>(sum, s_tmp, &turn, &total);
         ebase -= total;
-        repeats = __builtin_amdgcn_readfirstlane((int)a.repeats[bucket]) != 0;
+        repeats = __builtin_amdgcn_readfirstlane((int)a.repeats[u.bucket]) != 0;
     }
-    const bool here = n <= (uint32_t)S::CAP && (K > 0 || !repeats);
+    const bool here = u.shares == 1 && n <= (uint32_t)S::CAP && (K > 0 || !repeats);
     bool done = false;
     if (here)
-        done = bk_rows_lds<K, W, LARGE>(a, bucket, rec0, n, lo, nv, odd, elem && !repeats, ebase, s_val, s_start, s_cnt,
+        done = bk_rows_lds<K, W, LARGE>(a, u, rec0, n, lo, nv, odd, elem && !repeats, ebase, s_val, s_start, s_cnt,
                                         s_tmp, &turn, s_base);
-    if (K > 0 && node && !done)
-        bk_ranges<K, W, LARGE>(a, false, bucket, rec0, n, lo, nv, 0, s_val, s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
-    if (elem && (!done || repeats))
-        bk_ranges<K, W, LARGE>(a, true, bucket, rec0, n, lo, nv, ebase, s_val, s_start, s_cnt, s_pos, s_tmp, &turn,
-                               s_base);
+    // (where the rows of a share start follows from the counts only without repeats: the last share takes all)
+    const bool take = elem && (!done || repeats) && (!repeats || u.share + 1 == u.shares);
+#pragma unroll 1
+    for (int rel = K > 0 && node && !done ? 0 : 1; rel < (take ? 2 : 1); ++rel) {
+        BkUnit r = u;
+        if (rel == 1 && repeats) r.shares = 1;
+        bk_ranges<K, W, LARGE>(a, rel == 1, r, rec0, n, lo, nv, ebase, s_val, s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
+    }
+}
+
+// The unit of a ticket: a bucket, where no bucket has shares.
+__device__ __forceinline__ BkUnit bk_unit_of(uint32_t ticket, uint32_t n_unit, uint32_t n_bucket,
+                                             const uint32_t* __restrict__ units) {
+    BkUnit u{ticket, ticket, 0, 1, ticket + 1 == n_unit};
+    if (n_unit != n_bucket) {
+        u.bucket = (uint32_t)bk_find(units, (int)n_bucket, ticket);
+        const uint32_t u0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)units[u.bucket]);
+        u.share = ticket - u0;
+        u.shares = (uint32_t)__builtin_amdgcn_readfirstlane((int)units[u.bucket + 1]) - u0;
+    }
+    return u;
 }
 
 template <int K, int W, bool LARGE>
@@ -923,18 +1016,27 @@ void bk_rows_kernel(BkRowsArgs a) {
     using S = BkShape<K, LARGE>;
     __shared__ __align__(16) uint32_t s_all[BkLds<K, LARGE>::WORDS];
     __shared__ uint32_t s_tmp[2 * (S::BLOCK / WAVE)];
-    __shared__ uint32_t s_bucket;
+    __shared__ uint32_t s_ticket;
     __shared__ uint64_t s_base;
-    if (threadIdx.x == 0) s_bucket = atomicAdd(&a.hdr[HDR_BK_TICKET], 1u);  // so that every earlier bucket is already running
-    __syncthreads();
     // the same for every thread: scalar registers
-    const uint32_t bucket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bucket);
     const uint32_t odd = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.hdr[HDR_BK_ODD]);
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket]);
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[bucket + 1]) - r0;
-    const uint32_t lo = bk_first_vertex(bucket, a.mp.mul);
-    const uint32_t hi = bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_first_vertex(bucket + 1, a.mp.mul);
-    bk_bucket_rows<K, W, LARGE>(a, bucket, r0, n, r0, lo, (int)(hi - lo), odd, s_all, s_tmp, &s_base);
+    const uint32_t n_unit = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.hdr[HDR_BK_UNITS]);
+    do {
+        if (threadIdx.x == 0) s_ticket = atomicAdd(&a.hdr[HDR_BK_TICKET], 1u);  // so that every earlier unit is already running
+        __syncthreads();
+        const uint32_t ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_ticket);
+        if (ticket >= n_unit) return;
+        const BkUnit u = bk_unit_of(ticket, n_unit, a.mp.n_bucket, a.units);
+        const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[u.bucket]);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.starts[u.bucket + 1]) - r0;
+        uint32_t mul = a.mp.mul;
+        asm volatile("" : "+s"(mul));  // (as bk_tid)
+        const uint32_t lo = bk_first_vertex(u.bucket, mul);
+        const uint32_t hi = u.bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_first_vertex(u.bucket + 1, mul);
+        bk_unit_rows<K, W, LARGE>(a, u, r0, n, r0, lo, (int)(hi - lo), odd, s_all, s_tmp, &s_base);
+        if (n_unit == a.mp.n_bucket) return;  // (a block per bucket)
+        __syncthreads();                      // before the LDS is used again
+    } while (true);
 }
 
 }  // namespace mnb

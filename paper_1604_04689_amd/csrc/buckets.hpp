@@ -13,7 +13,8 @@
 //   bk_scan   where every block's pairs of a bucket go; bucket starts
 //   bk_part   conn -> records, each tile ordered by bucket in LDS, written at
 //             offsets that are known beforehand (no tile waits for another)
-//   bk_rows   one block per bucket: both CSRs (buckets.hpp's second half)
+//   bk_rows   one block per bucket, or several for one with many records:
+//             both CSRs (buckets.hpp's second half)
 //
 // Tiles are dealt to the XCDs in turn (tile t runs on XCD t mod 8 under the
 // usual round-robin dispatch), and a bucket's space is laid out by XCD first:
@@ -36,7 +37,9 @@ constexpr uint32_t BK_EMPTY = 0xffffffffu;  // never an id (ids are below 2^31)
 // Words of the workspace header this pipeline uses beyond the error word.
 constexpr int HDR_BK_SCAN = 34;    // bk_scan's block ticket
 constexpr int HDR_BK_ODD = 35;     // what bk_hist found (BK_BAD_ID, BK_HAS_DUP)
-constexpr int HDR_BK_TICKET = 36;  // bk_rows' bucket ticket
+constexpr int HDR_BK_TICKET = 36;  // bk_rows' unit ticket
+constexpr int HDR_BK_UNITS = 37;   // units of bk_rows: a bucket, or a share of one (bk_shares)
+constexpr int HDR_BK_PROGRESS = 38;  // steps of long units, for those that wait
 // Per-block findings of bk_hist.
 constexpr uint32_t BK_BAD_ID = 1u;   // an id outside [0, n_vert)
 constexpr uint32_t BK_HAS_DUP = 2u;  // an element repeats an id: it has more records than pairs
@@ -73,6 +76,32 @@ __host__ __device__ inline uint32_t bk_first_vertex(uint32_t bucket, uint32_t mu
     return (uint32_t)((((uint64_t)bucket << 32) + mul - 1) / mul);
 }
 __device__ __forceinline__ uint32_t bk_bucket(uint32_t v, uint32_t mul) { return __umulhi(v, mul); }
+
+// Blocks that share a bucket of n records.  Up to cap of them fit one block's
+// LDS.  Beyond, every share reads all of the bucket's records (to count them by
+// vertex, and to pick its own), so their number is bounded: 128 blocks that
+// read together are near what the caches give (about 50 GB/s each).
+constexpr uint32_t BK_SHARES = 128;
+__host__ __device__ inline uint32_t bk_shares(uint32_t n, uint32_t cap) {
+    return n <= cap ? 1u : tmin((n - 1) / (cap / 2) + 1, BK_SHARES);
+}
+// Most units that n_slots records in n_bucket buckets take.
+inline int64_t bk_unit_most(int64_t n_bucket, int64_t n_slots, int64_t cap) { return n_bucket + n_slots / (cap / 2) + 1; }
+
+// Largest i in [0, n) with off[i] <= x (off ascending from 0), found by a
+// whole wave, 64 places at a time.
+__device__ __forceinline__ int bk_find(const uint32_t* __restrict__ off, int n, uint32_t x) {
+    const int lane = __lane_id();
+    int lo = 0, len = n;
+    while (len > 1) {
+        const int step = (len + WAVE - 1) / WAVE;
+        const bool ok = lane * step < len && off[lo + lane * step] <= x;
+        const int k = (int)__popcll(__ballot(ok)) - 1;
+        lo += k * step;
+        len = tmin(step, len - k * step);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
 
 // A record holds the element (e_bits), the low bits of the vertex (vl_bits)
 // and its K neighbours (id_bits each) in W words, fewer words where they fit
@@ -233,7 +262,9 @@ __global__ __launch_bounds__(BLOCK) void bk_hist_kernel(const int32_t* __restric
 
 // ---- bk_scan ---------------------------------------------------------------------
 // btot[h][b] becomes the pairs of bucket b in the blocks before h (blocks in
-// the order x, then k), and starts[b] those of the buckets before b: a block
+// the order x, then k), starts[b] those of the buckets before b, and units[b]
+// the units of the buckets before b (read only where some bucket has shares;
+// summed above the pairs in one word): a block
 // (by ticket) takes 16 buckets, 64 threads per bucket, each a run of blocks
 // held in registers; the blocks' sums meet in a decoupled look-back.  (A last
 // block that scanned all totals needed device-wide fences, each a write-back
@@ -250,6 +281,7 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
                                                                   uint32_t n_bucket, uint32_t nb_pad,
                                                                   const uint32_t* __restrict__ flags,
                                                                   uint64_t* scan_lb, uint32_t* __restrict__ starts,
+                                                                  uint32_t* __restrict__ units, uint32_t bucket_cap,
                                                                   uint32_t rec_cap, uint64_t* __restrict__ lookback,
                                                                   uint32_t* __restrict__ repeats, uint32_t* hdr) {
     __shared__ uint32_t s_sum[BKS_ROWS][BKS_COLS + 1];
@@ -297,17 +329,25 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
         const uint32_t b = block * BKS_COLS + lane;
         const bool have = lane < BKS_COLS && b < n_bucket;
         const uint32_t t = have ? s_tot[lane] : 0u;
-        const uint32_t incl = wave_inclusive_sum(t);
-        const uint32_t all = __shfl(incl, WAVE - 1, WAVE);
-        if (lane == 0) lb_store(scan_lb + block, (block == 0 ? LB_INC : LB_AGG) | (uint64_t)all);
-        const uint32_t before = (uint32_t)wave_lookback_prefix(scan_lb, block, all, hdr + HDR_ERR);
+        const uint32_t more = have ? bk_shares(t, bucket_cap) - 1 : 0u;
+        const uint64_t mine = (uint64_t)more << 32 | t, incl = wave_inclusive_sum(mine);
+        const uint64_t all = __shfl(incl, WAVE - 1, WAVE);
+        if (lane == 0) lb_store(scan_lb + block, (block == 0 ? LB_INC : LB_AGG) | all);
+        const uint64_t before = wave_lookback_prefix(scan_lb, block, all, hdr + HDR_ERR);
         if (have) {
             // (never more than the records there is room for, which overlapping
             // elements of an ill-formed mixed mesh could ask for)
-            starts[b] = tmin(before + incl - t, rec_cap);
-            if (b + 1 == n_bucket) starts[n_bucket] = tmin(before + incl, rec_cap);
-            lookback[b] = 0;  // bk_rows'
-            repeats[b] = 0;   // counted by bk_part
+            const uint64_t to = before + incl, from = to - mine;
+            const uint32_t u = b + (uint32_t)(from >> 32);
+            starts[b] = tmin((uint32_t)from, rec_cap);
+            units[b] = u;
+            for (uint32_t i = 0; i <= more; ++i) lookback[u + i] = 0;  // bk_rows'
+            repeats[b] = 0;                                            // counted by bk_part
+            if (b + 1 == n_bucket) {
+                starts[n_bucket] = tmin((uint32_t)to, rec_cap);
+                units[n_bucket] = u + more + 1;
+                hdr[HDR_BK_UNITS] = u + more + 1;
+            }
         }
     }
     if (block != 0) return;

@@ -124,14 +124,16 @@ __device__ __forceinline__ uint64_t lookback_prefix(W* status, int64_t stride, u
 // The same for a single running count, walked by a whole wave: lane l reads
 // the status of tile (t - l), the wave finds the nearest inclusive value with
 // a ballot and sums the window with a wave reduction.  Every lane of the wave
-// must call it; all lanes return the prefix, lane 0 publishes.
-__device__ __forceinline__ uint64_t wave_lookback_prefix(uint64_t* status, uint32_t tile, uint64_t agg,
-                                                         uint32_t* err) {
+// must call it; all lanes return the prefix, lane 0 publishes.  Where a tile's
+// work has no small bound, its block counts its steps up in *progress, and the
+// wait gives up only when SPIN_LIMIT polls pass without one.
+__device__ __forceinline__ uint64_t wave_lookback_prefix(uint64_t* status, uint32_t tile, uint64_t agg, uint32_t* err,
+                                                         const uint32_t* progress = nullptr) {
     const int lane = __lane_id();
     if (tile == 0) return 0;
     uint64_t prefix = 0;
     int64_t t = (int64_t)tile - 1;  // newest tile of the window
-    uint32_t spins = 0;
+    uint32_t spins = 0, seen = 0;
     while (true) {
         const int64_t mine = t - lane;
         const uint64_t s = mine >= 0 ? lb_load(status + mine) : LB_INC;
@@ -141,7 +143,13 @@ __device__ __forceinline__ uint64_t wave_lookback_prefix(uint64_t* status, uint3
         // lanes up to and including the first inclusive one must be ready
         const uint64_t upto = inc ? ((inc & (~inc + 1)) << 1) - 1 : ~0ull;  // lanes 0..first INC
         if (none & upto) {
-            if (lookback_give_up(++spins, err)) {
+            ++spins;
+            if (progress && (spins & 4095u) == 0) {
+                const uint32_t now = (uint32_t)__builtin_amdgcn_readfirstlane((int)lb_load(progress));
+                if (now != seen) spins = 0;
+                seen = now;
+            }
+            if (lookback_give_up(spins, err)) {
                 if (lane == 0) set_error(err, ERR_INTERNAL);
                 break;
             }
