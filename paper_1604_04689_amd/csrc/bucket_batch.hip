@@ -518,8 +518,14 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
     take(&p->off_units, ((size_t)p->bucket_most + 1) * 4);
     take(&p->off_rep, (size_t)p->bucket_most * 4);
     take(&p->off_lb, (size_t)p->unit_most * 8);
-    take(&p->off_cells, (size_t)p->cell_most * 4);
     take(&p->off_rec, (size_t)p->word_most * 4);
+    take(&p->off_cells, (size_t)p->cell_most * 4);
+    // the lists of shared buckets over the counts, which are done with by then, if they fit
+    const size_t with_list = tmax(off, p->off_cells + align_up((size_t)total_slots * 4));
+    if (with_list <= limit) {
+        off = with_list;
+        p->off_list = p->off_cells;
+    }
     p->total = off;
     p->on = off <= limit && p->scan_most <= INT32_MAX && p->entries <= INT32_MAX && p->cell_most <= UINT32_MAX &&
             p->word_most / 2 <= UINT32_MAX;

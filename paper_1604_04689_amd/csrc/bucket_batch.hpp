@@ -32,7 +32,7 @@ struct BkBatchPlan {
     int32_t tile_slots = 0;  // most slots per tile
     int64_t entries = 0, bucket_most = 0, unit_most = 0, tile_most = 0, scan_most = 0, cell_most = 0, word_most = 0;
     size_t off_mesh = 0, off_tile0 = 0, off_scan0 = 0, off_bmesh = 0, off_tmesh = 0, off_starts = 0,
-           off_units = 0, off_rep = 0, off_lb = 0, off_cells = 0, off_rec = 0;
+           off_units = 0, off_rep = 0, off_lb = 0, off_cells = 0, off_rec = 0, off_list = 0;  // (no list: 0)
     size_t total = 0;
 };
 

@@ -93,12 +93,16 @@ void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* 
     off += align_up((size_t)m.n_bucket * sizeof(uint32_t));
     p->off_lb = off;
     off += align_up((size_t)bk_unit_most(m.n_bucket, p->n_elem * most_npe, bk_size(p->K, p->large).cap) * sizeof(uint64_t));
-    p->off_btot = off;
+    p->off_rec = off;
+    off += align_up(((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
+    p->off_btot = p->off_list = off;
     off += align_up((size_t)p->hist_blocks * m.nb_pad * sizeof(uint32_t));
     p->off_within = off;
     off += align_up((size_t)p->n_tiles * m.nb_pad * sizeof(uint16_t));
-    p->off_rec = off;
-    off += align_up(((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
+    // the lists of shared buckets over the counts, which are done with by then, if they fit
+    const size_t with_list = tmax(off, p->off_list + align_up((size_t)p->n_slots * sizeof(uint32_t)));
+    if (with_list <= limit) off = with_list;
+    else p->off_list = 0;
     p->total = off;
     p->on = off <= limit;
 }

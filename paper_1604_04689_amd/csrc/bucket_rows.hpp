@@ -288,6 +288,7 @@ struct BkRowsArgs {
     const uint32_t* units;    // first unit per bucket
     const uint32_t* repeats;  // per bucket: records whose pair an earlier record of the element has
     uint64_t* lookback;
+    uint32_t* list;  // a word per record for those of shared buckets (null: no room)
     uint32_t* hdr;
     int32_t* nrp;    // node CSR (null: not wanted)
     int32_t* ncols;
@@ -323,17 +324,6 @@ struct BkLds {
     static constexpr int VAL = S::POOL + BK_PAD;
     static constexpr int WORDS = VAL + (S::VMAX + 1) + (S::VMAX + 1) + S::VMAX / 2;
 };
-
-// Inclusive sum over the lanes of a wave (DPP: no LDS round trips).
-__device__ __forceinline__ uint32_t bk_wave_sum(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return x;
-}
 
 // Exclusive sum over the block with one barrier: *turn alternates between the
 // two halves of s_tmp (2 x BLOCK / 64 words), so that a call's reads are over
@@ -439,25 +429,28 @@ __device__ __forceinline__ uint64_t bk_before(const BkRowsArgs& a, uint32_t unit
     return *s_base;
 }
 
-// f(record) for the n records at rec, over the block, BK_AHEAD of a thread's
-// loads on their way at once.  Counts as a step for those that wait.
+// f(record, its place, its number in a turn) for the n records at rec, or for those that the n entries
+// of `list` name, over the block, BK_AHEAD of a thread's loads on their way at
+// once.  Counts as steps for those that wait.
 constexpr int BK_AHEAD = 8;
 constexpr uint32_t BK_STEP = 1u << 20;  // records of a step
 template <int W, int BLOCK, class F>
-__device__ __forceinline__ void bk_each_record(const BkRowsArgs& a, const uint32_t* rec, uint32_t n, F&& f) {
+__device__ __forceinline__ void bk_each_record(const BkRowsArgs& a, const uint32_t* rec, const uint32_t* list, uint32_t n,
+                                               F&& f) {
     for (uint32_t c0 = 0; c0 < n; c0 += BK_STEP) {
         if (bk_tid() == 0) atomicAdd(a.hdr + HDR_BK_PROGRESS, 1u);
-        const uint32_t m = tmin(n - c0, BK_STEP);
-        const uint32_t* at = rec + bk_record_at<W>(c0) / 4;
-        for (uint32_t i0 = (uint32_t)bk_tid(); i0 < m; i0 += BK_AHEAD * BLOCK) {
-            uint32_t r[BK_AHEAD][W];
+        const uint32_t end = c0 + tmin(n - c0, BK_STEP);
+        for (uint32_t i0 = c0 + (uint32_t)bk_tid(); i0 < end; i0 += BK_AHEAD * BLOCK) {
+            uint32_t at[BK_AHEAD], r[BK_AHEAD][W];
             bk_each<BK_AHEAD>([&](auto uu) BK_INLINE {
                 constexpr int u = decltype(uu)::value;
-                bk_load<W, true>(at, tmin(i0 + u * BLOCK, m - 1), r[u]);
+                at[u] = tmin(i0 + u * BLOCK, end - 1);
+                if (list) at[u] = list[at[u]];
             });
+            bk_each<BK_AHEAD>([&](auto uu) BK_INLINE { bk_load<W>(rec, at[decltype(uu)::value], r[decltype(uu)::value]); });
             bk_each<BK_AHEAD>([&](auto uu) BK_INLINE {
                 constexpr int u = decltype(uu)::value;
-                if (i0 + u * BLOCK < m) f(r[u]);
+                if (i0 + u * BLOCK < end) f(r[u], at[u], uu);
             });
         }
     }
@@ -543,12 +536,13 @@ __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s
     }
 }
 
-// Windows [wa, wb) of one row (vertex v of the bucket) beyond the LDS, each its
-// ids in a bit map of `words` words at s_map.  With write, they go to cols from
+// Windows [wa, wb) of one row (vertex v of the bucket) beyond the LDS, from the
+// records that bk_each_record takes, each its ids in a bit map of `words` words at s_map.  With write, they go to cols from
 // `at` on (as far as cap lets); for elements, which have no repeats where wa >
 // 0, `at` is where the whole row starts.  Returns their number.
 template <int K, int W, int BLOCK>
-__device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint32_t* rec, uint32_t n, uint32_t lo, int v,
+__device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint32_t* rec, const uint32_t* list,
+                                                uint32_t n, uint32_t lo, int v,
                                                 uint32_t wa, uint32_t wb, bool elements, uint32_t* s_map, uint32_t words,
                                                 uint32_t* s_tmp, int* turn, bool write, int32_t* cols, uint64_t at,
                                                 int64_t cap, bool* full) {
@@ -561,7 +555,7 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
         __syncthreads();
         for (uint32_t i = tid; i < words; i += BLOCK) s_map[i] = 0;
         __syncthreads();
-        bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
+        bk_each_record<W, BLOCK>(a, rec, list, n, [&](const uint32_t (&r)[W], uint32_t, auto) BK_INLINE {
             if (bk_row<K, W>(a.mp, r, lo) != (uint32_t)v) return;
             auto put = [&](uint32_t x) BK_INLINE {
                 const uint32_t o = x - w0;
@@ -605,9 +599,17 @@ __device__ __forceinline__ void bk_count_records(const BkRowsArgs& a, const uint
     __syncthreads();
     for (int v = tid; v < nv; v += BLOCK) s_start[v] = 0;
     __syncthreads();
-    bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
+    bool crowded = false;  // many lanes with one row, which would queue at its counter: one adds for them
+    bk_each_record<W, BLOCK>(a, rec, nullptr, n, [&](const uint32_t (&r)[W], uint32_t, auto uu) BK_INLINE {
         const uint32_t v = bk_row<K, W>(a.mp, r, lo);
-        if (v < (uint32_t)nv) atomicAdd(&s_start[v], 1u);
+        if (decltype(uu)::value == 0) crowded = bk_crowded(v);
+        uint32_t add = 1;
+        if (crowded) {
+            const uint32_t v0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+            const uint64_t same = __ballot(v == v0);
+            if (v == v0) add = (int)(bk_tid() & (WAVE - 1)) == __builtin_ctzll(same) ? (uint32_t)__popcll(same) : 0u;
+        }
+        if (v < (uint32_t)nv && add) atomicAdd(&s_start[v], add);
     });
     __syncthreads();
     bk_scan_lds<BLOCK, VMAX>(s_start, nv, s_tmp, turn);
@@ -634,13 +636,15 @@ __device__ __forceinline__ int bk_first_from(const uint32_t* s_start, int nv, ui
 // vertices whose records fit the LDS.  elements: the element rows, the bucket's
 // starting at `ebase`; else the node rows, which are counted first (a unit in
 // one range keeps them in the LDS meanwhile).  Share i takes the vertices whose
-// records start in the i-th part of the bucket's.  Every thread of the block
-// calls it.
+// records start in the i-th part of the bucket's, and lists them by vertex (at
+// `list`, if there is room), so that a range reads only its own.  `again`: the
+// unit has done its node rows here, and the counts and the list stand.  Every
+// thread of the block calls it.
 template <int K, int W, bool LARGE>
 __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, BkUnit u, int64_t rec0, uint32_t n,
-                                          uint32_t lo, int nv, uint64_t ebase, uint32_t* s_val, uint32_t* s_start,
-                                          uint32_t* s_cnt, uint16_t* s_pos, uint32_t* s_tmp, int* turn,
-                                          uint64_t* s_base) {
+                                          uint32_t lo, int nv, uint64_t ebase, uint32_t* list, bool again,
+                                          uint32_t* s_val, uint32_t* s_start, uint32_t* s_cnt, uint16_t* s_pos,
+                                          uint32_t* s_tmp, int* turn, uint64_t* s_base) {
     using S = BkShape<K, LARGE>;
     constexpr int BLOCK = S::BLOCK;
     constexpr uint32_t WINDOW = 32u * S::POOL;  // ids of a bit map
@@ -657,7 +661,7 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
     const int64_t cap = elements ? a.ecap : a.ncap;
     const uint32_t windows = (uint32_t)(((elements ? (uint64_t)a.n_elem : (uint64_t)a.mp.n_vert) + WINDOW - 1) / WINDOW);
     bool full = false;
-    bk_count_records<K, W, BLOCK, S::VMAX>(a, rec, n, lo, nv, s_start, s_tmp, turn);
+    if (!again) bk_count_records<K, W, BLOCK, S::VMAX>(a, rec, n, lo, nv, s_start, s_tmp, turn);
     int v0 = 0, v1 = nv;
     bool head = false;  // the share starts inside the row of vertex v0 - 1, beyond the LDS
     const uint32_t part = (n + u.shares - 1) / u.shares;
@@ -666,12 +670,29 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
         if (u.share + 1 < u.shares) v1 = bk_first_from(s_start, nv, (u.share + 1) * part);
         head = v0 > 0 && s_start[v0] > u.share * part && s_start[v0] - s_start[v0 - 1] > most;
     }
-    // the windows of long row v that share u takes: the row spans shares first .. end - 1
+    // the windows of long row v that share u takes, if it has a few shares: its first one
+    // has its records listed
     auto window = [&](int v, bool end) BK_INLINE {
-        if (u.shares == 1) return end ? windows : 0u;
         const uint32_t first = s_start[v] / part, shares = (s_start[v + 1] - 1) / part + 1 - first;
+        if (shares < 4) return u.shares > 1 && first != u.share ? windows : end ? windows : 0u;
         return (uint32_t)((uint64_t)windows * (u.share - first + (end ? 1 : 0)) / shares);
     };
+    // (the list takes one pass over all records: not for a share of one range, or of a
+    // row with most of them)
+    const uint32_t mine = s_start[v1] - s_start[v0];
+    if (u.shares == 1 || mine <= (again ? (uint32_t)S::POOL / (K > 0 ? K : 1) : most) || mine > 4 * part) list = nullptr;
+    if (list && !again) {
+        for (int v = v0 + tid; v < v1; v += BLOCK) s_cnt[v] = 0;
+        __syncthreads();
+        bk_each_record<W, BLOCK>(a, rec, nullptr, n, [&](const uint32_t (&r)[W], uint32_t i, auto) BK_INLINE {
+            const uint32_t v = bk_row<K, W>(a.mp, r, lo);
+            if (v >= (uint32_t)v0 && v < (uint32_t)v1) list[s_start[v] + atomicAdd(&s_cnt[v], 1u)] = i;
+        });
+        __syncthreads();
+    }
+    // what bk_each_record takes for vertices [va, vb) of the share's own
+    auto own = [&](int va) BK_INLINE { return list && va >= v0 ? list + s_start[va] : nullptr; };
+    auto records = [&](int va, int vb) BK_INLINE { return list && va >= v0 ? s_start[vb] - s_start[va] : n; };
     const bool single = !head && (v0 == v1 || bk_range_end(s_start, v0, v1, most) == v1);
     uint64_t base = ebase, run = 0;
     if (elements) base += s_start[head ? v0 - 1 : v0];
@@ -683,8 +704,8 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
             const uint64_t at = base + run;
             if (vb == va) {
                 if (phase == 1 && va >= v0 && tid == 0) rp[lo + va] = (int32_t)at;
-                run += bk_huge_row<K, W, BLOCK>(a, rec, n, lo, va, window(va, false), window(va, true), elements, s_val,
-                                                (uint32_t)S::POOL, s_tmp, turn, phase == 1, cols, at, cap, &full);
+                run += bk_huge_row<K, W, BLOCK>(a, rec, own(va), records(va, va + 1), lo, va, window(va, false),
+                                                window(va, true), elements, s_val, (uint32_t)S::POOL, s_tmp, turn, phase == 1, cols, at, cap, &full);
                 ++va;
                 if (elements && u.shares > 1) run = ebase + s_start[va] - base;  // (its end, if here; else nothing follows)
                 continue;
@@ -693,7 +714,7 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
             if (phase == 0 || elements || !single) {
                 for (int v = va + tid; v < vb; v += BLOCK) s_cnt[v] = 0;
                 __syncthreads();
-                bk_each_record<W, BLOCK>(a, rec, n, [&](const uint32_t (&r)[W]) BK_INLINE {
+                bk_each_record<W, BLOCK>(a, rec, own(va), records(va, vb), [&](const uint32_t (&r)[W], uint32_t, auto) BK_INLINE {
                     const uint32_t v = bk_row<K, W>(a.mp, r, lo);
                     if (v < (uint32_t)va || v >= (uint32_t)vb) return;
                     const uint32_t slot = s_start[v] - s0 + atomicAdd(&s_cnt[v], 1u);
@@ -990,10 +1011,11 @@ __device__ __forceinline__ void bk_unit_rows(const BkRowsArgs& a, const BkUnit& 
     // (where the rows of a share start follows from the counts only without repeats: the last share takes all)
     const bool take = elem && (!done || repeats) && (!repeats || u.share + 1 == u.shares);
 #pragma unroll 1
-    for (int rel = K > 0 && node && !done ? 0 : 1; rel < (take ? 2 : 1); ++rel) {
+    for (int rel = K > 0 && node && !done ? 0 : 1, from = rel; rel < (take ? 2 : 1); ++rel) {
         BkUnit r = u;
         if (rel == 1 && repeats) r.shares = 1;
-        bk_ranges<K, W, LARGE>(a, rel == 1, r, rec0, n, lo, nv, ebase, s_val, s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
+        bk_ranges<K, W, LARGE>(a, rel == 1, r, rec0, n, lo, nv, ebase, a.list ? a.list + r0 : nullptr, rel != from, s_val,
+                               s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
     }
 }
 

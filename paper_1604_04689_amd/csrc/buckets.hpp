@@ -88,6 +88,17 @@ __host__ __device__ inline uint32_t bk_shares(uint32_t n, uint32_t cap) {
 // Most units that n_slots records in n_bucket buckets take.
 inline int64_t bk_unit_most(int64_t n_bucket, int64_t n_slots, int64_t cap) { return n_bucket + n_slots / (cap / 2) + 1; }
 
+// Inclusive sum over the lanes of a wave (DPP: no LDS round trips).
+__device__ __forceinline__ uint32_t bk_wave_sum(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
 // Largest i in [0, n) with off[i] <= x (off ascending from 0), found by a
 // whole wave, 64 places at a time.
 __device__ __forceinline__ int bk_find(const uint32_t* __restrict__ off, int n, uint32_t x) {
@@ -330,8 +341,9 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
         const bool have = lane < BKS_COLS && b < n_bucket;
         const uint32_t t = have ? s_tot[lane] : 0u;
         const uint32_t more = have ? bk_shares(t, bucket_cap) - 1 : 0u;
-        const uint64_t mine = (uint64_t)more << 32 | t, incl = wave_inclusive_sum(mine);
-        const uint64_t all = __shfl(incl, WAVE - 1, WAVE);
+        const uint64_t mine = (uint64_t)more << 32 | t, incl = (uint64_t)bk_wave_sum(more) << 32 | bk_wave_sum(t);
+        const uint64_t all = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(incl >> 32), WAVE - 1) << 32 |
+                             (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
         if (lane == 0) lb_store(scan_lb + block, (block == 0 ? LB_INC : LB_AGG) | all);
         const uint64_t before = wave_lookback_prefix(scan_lb, block, all, hdr + HDR_ERR);
         if (have) {

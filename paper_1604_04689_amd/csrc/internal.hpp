@@ -170,7 +170,7 @@ struct BkPlan {
     int R = 1;                // tiles per bk_hist block
     int hist_blocks = 0;
     size_t off_flags = 0, off_scan = 0, off_starts = 0, off_units = 0, off_rep = 0, off_lb = 0, off_btot = 0, off_within = 0,
-           off_rec = 0;
+           off_rec = 0, off_list = 0;  // (no list: 0)
     size_t total = 0;
 };
 // Plans the bucket pipeline into at most `limit` workspace bytes; p->on says
