@@ -27,6 +27,7 @@ BkSize bk_size(int K, bool large) {
         constexpr int K = decltype(k)::value;
         using S = BkShape<K, decltype(l)::value>;
         static_assert((K > 0 ? K : 1) * S::CAP <= S::POOL && S::POOL < 65536, "a full bucket fits the pool; 16-bit places");
+        static_assert(S::POOL % (2 * (S::BLOCK / WAVE)) == 0, "a wave's part of a bit map is whole 64-bit words");
         return BkSize{S::CAP, S::VMAX};
     });
 }

@@ -169,40 +169,69 @@ __device__ __forceinline__ void bk_wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// A wave sorts a[0 .. n), n <= 64 E, in registers (bitonic, E values per lane,
-// value r * 64 + lane in x[r]) and writes the distinct values other than
-// BK_EMPTY back to the front; returns their number.  About 1.5 us for 64
-// values where the same in LDS took 10 (a round trip per step).
+// A wave sorts its 64 E values in registers (bitonic, E values per lane, value
+// r * 64 + lane in x[r]).  Steps between lanes go in loops that are not unrolled
+// where E is large: unrolled, 2048 values would take 10,000 instructions.
 template <int E>
-__device__ __forceinline__ uint32_t bk_wave_sort_unique(uint32_t* a, uint32_t n) {
+__device__ __forceinline__ void bk_wave_sort(uint32_t (&x)[E]) {
+    const int lane = bk_tid() & (WAVE - 1);
+    constexpr int UNROLL = E <= 4 ? 6 : 1;
+    // (up: which registers' runs ascend; kept out of the loop over them)
+    auto between_lanes = [&](int j, bool up_even, bool up_odd, auto odd) BK_INLINE {
+        const bool low = (lane & j) == 0, even_low = up_even == low, odd_low = up_odd == low;
+        bk_each<E>([&](auto rr) BK_INLINE {
+            constexpr int r = decltype(rr)::value;
+            const uint32_t y = (uint32_t)__shfl_xor((int)x[r], j, WAVE);
+            const uint32_t lo = min(x[r], y), hi = max(x[r], y);
+            x[r] = (odd(rr) ? odd_low : even_low) ? lo : hi;
+        });
+    };
+#pragma unroll UNROLL
+    for (int k = 2; k <= WAVE; k *= 2)
+#pragma unroll UNROLL
+        for (int j = k / 2; j > 0; j /= 2)
+            between_lanes(j, (lane & k) == 0, k < WAVE && (lane & k) == 0, [](auto rr) BK_INLINE { return (decltype(rr)::value & 1) != 0; });
+    auto runs = [&](auto kk) BK_INLINE {  // runs of K registers from runs of K / 2
+        constexpr int K = decltype(kk)::value;
+#pragma unroll
+        for (int j = K / 2; j > 0; j /= 2)
+            bk_each<E>([&](auto rr) BK_INLINE {
+                constexpr int r = decltype(rr)::value;
+                const int q = r ^ j;
+                if (q > r) {
+                    const uint32_t lo = min(x[r], x[q < E ? q : r]), hi = max(x[r], x[q < E ? q : r]);
+                    const bool up = (r & K) == 0;
+                    x[r] = up ? lo : hi;
+                    x[q < E ? q : r] = up ? hi : lo;
+                }
+            });
+#pragma unroll UNROLL
+        for (int j = WAVE / 2; j > 0; j /= 2)
+            between_lanes(j, true, false, [](auto rr) BK_INLINE { return (decltype(rr)::value & K) != 0; });
+    };
+    if constexpr (E >= 2) runs(std::integral_constant<int, 2>{});
+    if constexpr (E >= 4) runs(std::integral_constant<int, 4>{});
+    if constexpr (E >= 8) runs(std::integral_constant<int, 8>{});
+    if constexpr (E >= 16) runs(std::integral_constant<int, 16>{});
+    if constexpr (E >= 32) runs(std::integral_constant<int, 32>{});
+}
+template <int E>
+__device__ __forceinline__ void bk_wave_load(const uint32_t* a, uint32_t n, uint32_t (&x)[E]) {
     const uint32_t lane = (uint32_t)(bk_tid() & (WAVE - 1));
-    uint32_t x[E];
     bk_each<E>([&](auto rr) BK_INLINE {
         constexpr int r = decltype(rr)::value;
         x[r] = r * WAVE + lane < n ? a[r * WAVE + lane] : BK_EMPTY;
     });
-#pragma unroll
-    for (int k = 2; k <= WAVE * E; k *= 2) {
-#pragma unroll
-        for (int j = k / 2; j > 0; j /= 2) {
-            bk_each<E>([&](auto rr) BK_INLINE {
-                constexpr int r = decltype(rr)::value;
-                if (j >= WAVE) {
-                    const int q = r ^ (j / WAVE);
-                    if (q > r) {
-                        const uint32_t lo = min(x[r], x[q < E ? q : r]), hi = max(x[r], x[q < E ? q : r]);
-                        const bool up = ((r * WAVE) & k) == 0;
-                        x[r] = up ? lo : hi;
-                        x[q < E ? q : r] = up ? hi : lo;
-                    }
-                } else {
-                    const uint32_t y = (uint32_t)__shfl_xor((int)x[r], j, WAVE);
-                    const bool up = ((r * WAVE + lane) & k) == 0, low = (lane & j) == 0;
-                    x[r] = up == low ? min(x[r], y) : max(x[r], y);
-                }
-            });
-        }
-    }
+}
+// A wave sorts a[0 .. n), n <= 64 E, and writes the distinct values other than
+// BK_EMPTY back to the front; returns their number.  About 1.5 us for 64 values
+// where the same in LDS took 10 (a round trip per step).
+template <int E>
+__device__ __forceinline__ uint32_t bk_wave_sort_unique(uint32_t* a, uint32_t n) {
+    const uint32_t lane = (uint32_t)(bk_tid() & (WAVE - 1));
+    uint32_t x[E];
+    bk_wave_load(a, n, x);
+    bk_wave_sort(x);
     uint32_t cnt = 0, prev = BK_EMPTY;
     bk_wave_sync();
     bk_each<E>([&](auto rr) BK_INLINE {
@@ -218,19 +247,33 @@ __device__ __forceinline__ uint32_t bk_wave_sort_unique(uint32_t* a, uint32_t n)
     bk_wave_sync();
     return cnt;
 }
+constexpr uint32_t BK_WAVE_ROW = 2048;  // values that a wave sorts in registers
 
-// Batcher's network over a[0 .. n) in LDS, any n, by THREADS threads (a wave
-// or the whole block), then the distinct values other than BK_EMPTY compacted
-// to the front by the calling wave(s)' first wave.  Returns their number in
-// every lane of that wave.
-template <bool BLOCKWIDE, int THREADS>
-__device__ inline uint32_t bk_lds_sort_unique(uint32_t* a, uint32_t n) {
-    const uint32_t me = BLOCKWIDE ? (uint32_t)bk_tid() : (uint32_t)(bk_tid() & (WAVE - 1));
-    auto sync = [] {
-        if constexpr (BLOCKWIDE) __syncthreads();
-        else bk_wave_sync();
-    };
-    for (uint32_t p = 1; p < n; p *= 2) {
+// Every 64 E values of a[0 .. n) sorted by a wave in registers.
+template <int E, int THREADS>
+__device__ __forceinline__ uint32_t bk_sort_pieces(uint32_t* a, uint32_t n) {
+    const uint32_t me = (uint32_t)bk_tid();
+    for (uint32_t c0 = me / WAVE * (E * WAVE); c0 < n; c0 += THREADS * E) {
+        uint32_t x[E];
+        bk_wave_load(a + c0, n - c0, x);
+        bk_wave_sort(x);
+        bk_each<E>([&](auto rr) BK_INLINE {
+            constexpr int r = decltype(rr)::value;
+            const uint32_t i = c0 + r * WAVE + (me & (WAVE - 1));
+            if (i < n) a[i] = x[r];
+        });
+    }
+    __syncthreads();
+    return E * WAVE;
+}
+// The block sorts a[0 .. n) in LDS, any n: pieces by the waves, in registers,
+// then the rest of Batcher's network.  The first wave writes the distinct
+// values other than BK_EMPTY back to the front; returns their number in its
+// lanes.  (The whole network in LDS took 66 steps, about 50 us, for 2000 values.)
+template <int THREADS>
+__device__ __forceinline__ uint32_t bk_block_sort_unique(uint32_t* a, uint32_t n) {
+    const uint32_t me = (uint32_t)bk_tid();
+    for (uint32_t p = n <= 4 * THREADS ? bk_sort_pieces<4, THREADS>(a, n) : bk_sort_pieces<16, THREADS>(a, n); p < n; p *= 2) {
         for (uint32_t k = p; k >= 1; k /= 2) {
             const uint32_t j0 = k == p ? 0u : k;
             // comparator c of the step: x and x + k (k is a power of two)
@@ -245,11 +288,11 @@ __device__ inline uint32_t bk_lds_sort_unique(uint32_t* a, uint32_t n) {
                     }
                 }
             }
-            sync();
+            __syncthreads();
         }
     }
     uint32_t cnt = 0;
-    if (!BLOCKWIDE || bk_tid() < WAVE) {
+    if (bk_tid() < WAVE) {
         const uint32_t lane = (uint32_t)(bk_tid() & (WAVE - 1));
         const uint64_t lt = (1ull << lane) - 1;
         uint32_t prev = BK_EMPTY;
@@ -266,18 +309,33 @@ __device__ inline uint32_t bk_lds_sort_unique(uint32_t* a, uint32_t n) {
             cnt += (uint32_t)__popcll(m);
         }
     }
-    sync();
+    __syncthreads();
     return cnt;
 }
 
-// A row by one wave, sorted without repeats.
+// A row of up to MOST values by one wave, sorted without repeats.
+template <uint32_t MOST = BK_WAVE_ROW>
 __device__ __forceinline__ uint32_t bk_wave_row(uint32_t* a, uint32_t n) {
     n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
     if (n <= 64) return bk_wave_sort_unique<1>(a, n);
     if (n <= 128) return bk_wave_sort_unique<2>(a, n);
     if (n <= 256) return bk_wave_sort_unique<4>(a, n);
-    if (n <= 512) return bk_wave_sort_unique<8>(a, n);
-    return bk_lds_sort_unique<false, WAVE>(a, n);
+    if (MOST <= 512 || n <= 512) return bk_wave_sort_unique<8>(a, n);
+    if constexpr (MOST > 512) return bk_wave_sort_unique<(int)BK_WAVE_ROW / WAVE>(a, n);
+}
+
+// Rows that a wave takes for itself: where few of rows [va, vb) have more than
+// 512 values, the whole block sorts each of those (2000 values in about 10 us,
+// where a wave alone takes 20).
+template <int BLOCK, class Len>
+__device__ __forceinline__ uint32_t bk_wave_most(int va, int vb, Len&& len) {
+    int many = 0;
+    for (int v0 = va; v0 < vb; v0 += WAVE) {
+        const int v = v0 + (bk_tid() & (WAVE - 1));
+        const uint32_t n = v < vb ? len(v) : 0u;
+        many += (int)__popcll(__ballot(n > 512 && n <= BK_WAVE_ROW));
+    }
+    return 2 * many > BLOCK / WAVE ? BK_WAVE_ROW : 512u;
 }
 
 // ---- bk_rows -----------------------------------------------------------------
@@ -487,12 +545,12 @@ __device__ __forceinline__ bool bk_row_windows(uint32_t*& src, uint32_t& left, u
 
 // Rows [va, vb), row v's `per` values per record at s_val + per * (s_start[v]
 // - s0): each sorted without repeats, its first value at s_pos[v], its count
-// in s_cnt[v].  Rows beyond a window are sorted in LDS, by a wave up to 1024
-// values, by the block beyond.  All threads; starts and ends with a barrier.
+// in s_cnt[v].  Rows beyond a window are sorted by a wave or the
+// block (bk_wave_most).  All threads; starts and ends with a barrier.
 template <int BLOCK>
 __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s_start, uint32_t s0, int va, int vb,
                                               uint32_t per, uint32_t* s_cnt, uint16_t* s_pos) {
-    constexpr uint32_t LONG = 1u << 31, DONE = 1u << 30, WAVE_MAX = 1024;
+    constexpr uint32_t LONG = 1u << 31, DONE = 1u << 30;
     const int tid = bk_tid(), lane = tid & (WAVE - 1), wid = tid / WAVE;
     __syncthreads();
     for (int v0 = va + wid * WAVE; v0 < vb; v0 += BLOCK) {
@@ -509,10 +567,12 @@ __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s
         }
     }
     __syncthreads();
+    const uint32_t wave_most = bk_wave_most<BLOCK>(va, vb, [&](int v) BK_INLINE { return s_cnt[v] & LONG ? s_cnt[v] & ~LONG : 0u; });
+    __syncthreads();  // (before a wave marks one done)
     for (int v0 = va, i = 0; v0 < vb; v0 += WAVE) {  // the waves take the longer rows in turn
         const uint32_t f = v0 + lane < vb ? s_cnt[v0 + lane] : 0u;
         // (a row that another wave has done meanwhile is still marked, so that all count alike)
-        const bool wave_row = (f & LONG) && ((f & DONE) || (f & ~LONG) <= WAVE_MAX);
+        const bool wave_row = (f & LONG) && ((f & DONE) || (f & ~LONG) <= wave_most);
         for (uint64_t m = __ballot(wave_row); m; m &= m - 1, ++i) {
             const int l = __builtin_ctzll(m);
             if (i % (BLOCK / WAVE) != wid) continue;
@@ -530,7 +590,7 @@ __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s
         const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cnt[v]);
         if (!(n & LONG)) continue;
         __syncthreads();  // (every wave has seen the mark)
-        const uint32_t c = bk_lds_sort_unique<true, BLOCK>(s_val + s_pos[v], n & ~LONG);
+        const uint32_t c = bk_block_sort_unique<BLOCK>(s_val + s_pos[v], n & ~LONG);
         if (tid == 0) s_cnt[v] = c;
         __syncthreads();
     }
@@ -547,7 +607,7 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
                                                 uint32_t* s_tmp, int* turn, bool write, int32_t* cols, uint64_t at,
                                                 int64_t cap, bool* full) {
     const int tid = bk_tid();
-    const uint32_t per = (words + BLOCK - 1) / BLOCK;
+    const uint32_t per = words / (BLOCK / WAVE);  // (even: a static_assert with the shapes)
     uint32_t all = 0;
     for (uint32_t w = wa; w < wb; ++w) {
         const uint32_t w0 = w * 32 * words;  // (below 2^31: an id)
@@ -573,18 +633,39 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
             }
         });
         __syncthreads();
+        // a wave has a run of the map
+        const int lane = tid & (WAVE - 1);
+        const uint32_t* const map = s_map + (uint32_t)tid / WAVE * per;
         uint32_t c = 0;
-        for (uint32_t i = tid * per; i < tmin<uint32_t>((tid + 1) * per, words); ++i) c += (uint32_t)__popc(s_map[i]);
+        for (uint32_t i = lane; i < per; i += WAVE) c += (uint32_t)__popc(map[i]);
         uint32_t total, skip = 0;
         if (elements && w == wa && wa > 0) bk_block_sum<BLOCK>(below, s_tmp, turn, &skip);
         at += skip;
-        uint64_t d = at + all + bk_block_sum<BLOCK>(c, s_tmp, turn, &total);
-        if (write)
-            for (uint32_t i = tid * per; i < tmin<uint32_t>((tid + 1) * per, words); ++i)
-                for (uint32_t m = s_map[i]; m; m &= m - 1, ++d) {
-                    if ((int64_t)d < cap) cols[d] = (int32_t)(w0 + 32 * i + __builtin_ctz(m));
-                    else *full = true;
+        uint32_t place = bk_block_sum<BLOCK>(c, s_tmp, turn, &total);
+        place = (uint32_t)__builtin_amdgcn_readfirstlane((int)place);
+        for (uint32_t i0 = 0; write && i0 < per; i0 += 2 * WAVE) {  // 64 ids per lane
+            const uint32_t i = i0 + 2 * lane, id0 = w0 + 32 * ((uint32_t)tid / WAVE * per + i0);
+            uint64_t m = i < per ? (uint64_t)map[i + 1] << 32 | map[i] : 0ull;
+            const uint32_t mine = (uint32_t)__popcll(m), upto = bk_wave_sum(mine);
+            auto put = [&](uint64_t d, uint32_t id) BK_INLINE {
+                if ((int64_t)d < cap) cols[d] = (int32_t)id;
+                else *full = true;
+            };
+            if (!__ballot(mine > 16)) {
+                for (uint64_t d = at + all + place + upto - mine; m; m &= m - 1) put(d++, id0 + 64 * lane + __builtin_ctzll(m));
+            } else {  // many of them: a lane's go out side by side, by the wave
+                const uint32_t hi = (uint32_t)(m >> 32), lo32 = (uint32_t)m;
+                uint64_t d = at + all + place;
+                for (uint64_t l64 = __ballot(m != 0); l64; l64 &= l64 - 1) {
+                    const int l = __builtin_ctzll(l64);
+                    const uint32_t h = (uint32_t)__builtin_amdgcn_readlane((int)hi, l), o = (uint32_t)__builtin_amdgcn_readlane((int)lo32, l);
+                    const uint64_t q = (uint64_t)h << 32 | o;
+                    if (q >> lane & 1) put(d + __builtin_amdgcn_mbcnt_hi(h, __builtin_amdgcn_mbcnt_lo(o, 0u)), id0 + 64 * l + lane);
+                    d += (uint32_t)__popcll(q);
                 }
+            }
+            place += (uint32_t)__builtin_amdgcn_readlane((int)upto, WAVE - 1);
+        }
         all += total;
     }
     __syncthreads();
@@ -847,7 +928,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
         // too many distinct values: more than all rows of a bucket keep (K * CAP is at
         // most POOL), and small enough that the sum of a whole block of marks and of all
         // kept values stays below 2^32
-        constexpr uint32_t STUCK = S::POOL + 1;
+        constexpr uint32_t STUCK = S::POOL + 1, MID_ROW = 512;
         static_assert(K * CAP <= S::POOL && (uint64_t)BLOCK * STUCK + S::POOL <= UINT32_MAX, "marks never cancel out");
         auto rows = [&](auto most) BK_INLINE {  // rounds of up to `most` values
             constexpr int MOST = decltype(most)::value;
@@ -869,7 +950,9 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
                     for (uint64_t m = __ballot(!fits); m; m &= m - 1) {
                         const int l = __builtin_ctzll(m);
                         uint32_t* const a0 = s_val + __builtin_amdgcn_readlane((int)(src - s_val), l);
-                        const uint32_t cl = bk_wave_row(a0, (uint32_t)__builtin_amdgcn_readlane((int)left, l));
+                        const uint32_t n0 = (uint32_t)__builtin_amdgcn_readlane((int)left, l);
+                        // (no mesh's row of that many values keeps 64)
+                        const uint32_t cl = n0 > MID_ROW ? STUCK : bk_wave_row<MID_ROW>(a0, n0);
                         const bool wide_row = cl > (uint32_t)MOST;
                         if ((tid & (WAVE - 1)) == l) c = wide_row && (cl > 64 || spread >= 0) ? STUCK : cl;
                         if (wide_row && spread < 0) {
@@ -936,18 +1019,19 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
                 });
             });
         }
-        if (bk_any<BLOCK>(lng, s_tmp, turn)) {  // longer rows: a wave each up to 1024 elements, the block beyond
+        if (bk_any<BLOCK>(lng, s_tmp, turn)) {  // longer rows: a wave each, or the block
+            const uint32_t wave_most = bk_wave_most<BLOCK>(0, nv, deg);
             for (int v0 = 0; v0 < nv; v0 += WAVE) {
                 const int v = v0 + (tid & (WAVE - 1));
                 const uint32_t d = v < nv ? deg(v) : 0u;
-                uint64_t m = __ballot(d > BK_NET_MAX && d <= 1024);
+                uint64_t m = __ballot(d > BK_NET_MAX && d <= wave_most);
                 for (int i = 0; m; m &= m - 1, ++i) {
                     const int u = v0 + __builtin_ctzll(m);
                     if (i % (BLOCK / WAVE) == tid / WAVE) bk_wave_row(s_elem + s_start[u], deg(u));
                 }
-                for (m = __ballot(d > 1024); m; m &= m - 1) {
+                for (m = __ballot(d > wave_most); m; m &= m - 1) {
                     const int u = v0 + __builtin_ctzll(m);
-                    bk_lds_sort_unique<true, BLOCK>(s_elem + s_start[u], deg(u));
+                    bk_block_sort_unique<BLOCK>(s_elem + s_start[u], deg(u));
                 }
             }
             __syncthreads();
