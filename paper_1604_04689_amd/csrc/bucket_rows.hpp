@@ -839,12 +839,14 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
 }
 
 // A bucket of at most CAP records over nv vertices, from registers and LDS.
-// False where its node rows are left to bk_ranges, and the element rows too, with
-// nothing announced or written yet: a row of more than 64 distinct values, or a
-// second one of more than 32 among 64 rows.
+// Which relations are done: none where a node row is left to bk_ranges, with
+// nothing announced or written yet (a row of more than 64 distinct values, or a
+// second one of more than 32 among 64 rows), and no element rows where the bucket
+// has repeats (of a vertex in an element) and a row beyond the networks.
+constexpr int BK_NODE_DONE = 1, BK_ELEM_DONE = 2;
 template <int K, int W, bool LARGE>
-__device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u, int64_t rec0, uint32_t n, uint32_t lo,
-                                            int nv, uint32_t odd, bool elem, uint64_t ebase, uint32_t* s_val,
+__device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u, int64_t rec0, uint32_t n, uint32_t lo,
+                                            int nv, uint32_t odd, bool elem, bool repeats, uint64_t ebase, uint32_t* s_val,
                                             uint32_t* s_start,
                                             uint32_t* s_cnt, uint32_t* s_tmp, int* turn, uint64_t* s_base) {
     using S = BkShape<K, LARGE>;
@@ -983,7 +985,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
         };
         if (wide) rows(std::integral_constant<int, (int)BK_NET_MAX>{});
         else rows(std::integral_constant<int, 16>{});
-        if (total >= STUCK) return false;  // a row beyond the networks
+        if (total >= STUCK) return 0;  // a row beyond the networks
         bk_publish(a, u.unit, total);
     }
     bool full = false;
@@ -1033,7 +1035,8 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
                 });
             });
         }
-        if (bk_any<BLOCK>(lng, s_tmp, turn)) {  // longer rows: a wave each, or the block
+        lng = bk_any<BLOCK>(lng, s_tmp, turn);
+        if (lng && !repeats) {  // longer rows: a wave each, or the block
             const uint32_t wave_most = bk_wave_most<BLOCK>(0, nv, deg);
             for (int v0 = 0; v0 < nv; v0 += WAVE) {
                 const int v = v0 + (tid & (WAVE - 1));
@@ -1050,11 +1053,31 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
             }
             __syncthreads();
         }
-        for (int v = tid; v < nv; v += BLOCK) a.erp[lo + v] = (int32_t)(ebase + s_start[v]);
-        if (u.last && tid == 0) a.erp[a.mp.n_vert] = (int32_t)(ebase + n);
-        if ((int64_t)(ebase + n) > a.ecap) full = true;
-        else
-            for (uint32_t i = tid; i < n; i += BLOCK) a.ecols[ebase + i] = (int32_t)s_elem[i];
+        if (repeats && !lng) {  // (seldom) what is left of each row, by its thread
+            uint32_t run = 0;
+            for (int v0 = 0; v0 < nv; v0 += BLOCK) {
+                const int v = v0 + tid;
+                const uint32_t d = v < nv ? deg(v) : 0u;
+                const uint32_t* const src = s_elem + (v < nv ? s_start[v] : 0u);
+                uint32_t c = 0, sum;
+                for (uint32_t i = 0; i < d; ++i) c += i == 0 || src[i] != src[i - 1] ? 1u : 0u;
+                uint64_t at = ebase + run + bk_block_sum<BLOCK>(c, s_tmp, turn, &sum);
+                run += sum;
+                if (v < nv) a.erp[lo + v] = (int32_t)at;
+                if ((int64_t)(at + c) > a.ecap) full = true;
+                else
+                    for (uint32_t i = 0; i < d; ++i)
+                        if (i == 0 || src[i] != src[i - 1]) a.ecols[at++] = (int32_t)src[i];
+            }
+            if (u.last && tid == 0) a.erp[a.mp.n_vert] = (int32_t)(ebase + run);
+        } else if (!repeats) {
+            for (int v = tid; v < nv; v += BLOCK) a.erp[lo + v] = (int32_t)(ebase + s_start[v]);
+            if (u.last && tid == 0) a.erp[a.mp.n_vert] = (int32_t)(ebase + n);
+            if ((int64_t)(ebase + n) > a.ecap) full = true;
+            else
+                for (uint32_t i = tid; i < n; i += BLOCK) a.ecols[ebase + i] = (int32_t)s_elem[i];
+        }
+        elem = !(repeats && lng);
     }
 
     // ---- node rows out
@@ -1062,7 +1085,7 @@ __device__ __forceinline__ bool bk_rows_lds(const BkRowsArgs& a, const BkUnit& u
     if (full) set_error(a.hdr + HDR_ERR, ERR_CAPACITY);
     // (records beyond the room there is, of an ill-formed mixed mesh, are missing)
     if (bad && !(odd & BK_BAD_ID)) set_error(a.hdr + HDR_ERR, ERR_INTERNAL);
-    return true;
+    return BK_NODE_DONE | (elem ? BK_ELEM_DONE : 0);
 }
 
 // Unit u, of a bucket of n records from rec0 on, the r0-th pair of all: both its
@@ -1094,15 +1117,15 @@ __device__ __forceinline__ void bk_unit_rows(const BkRowsArgs& a, const BkUnit& 
         ebase -= total;
         repeats = __builtin_amdgcn_readfirstlane((int)a.repeats[u.bucket]) != 0;
     }
-    const bool here = u.shares == 1 && n <= (uint32_t)S::CAP && (K > 0 || !repeats);
-    bool done = false;
-    if (here)
-        done = bk_rows_lds<K, W, LARGE>(a, u, rec0, n, lo, nv, odd, elem && !repeats, ebase, s_val, s_start, s_cnt,
-                                        s_tmp, &turn, s_base);
+    int done = 0;
+    if (u.shares == 1 && n <= (uint32_t)S::CAP)
+        done = bk_rows_lds<K, W, LARGE>(a, u, rec0, n, lo, nv, odd, elem, repeats, ebase, s_val, s_start, s_cnt, s_tmp, &turn,
+                                        s_base);
+    const bool node_left = node && !(done & BK_NODE_DONE);
     // (where the rows of a share start follows from the counts only without repeats: the last share takes all)
-    const bool take = elem && (!done || repeats) && (!repeats || u.share + 1 == u.shares);
+    const bool elem_left = elem && !(done & BK_ELEM_DONE) && (!repeats || u.share + 1 == u.shares);
 #pragma unroll 1
-    for (int rel = K > 0 && node && !done ? 0 : 1, from = rel; rel < (take ? 2 : 1); ++rel) {
+    for (int rel = node_left ? 0 : 1, from = rel; rel < (elem_left ? 2 : 1); ++rel) {
         BkUnit r = u;
         if (rel == 1 && repeats) r.shares = 1;
         bk_ranges<K, W, LARGE>(a, rel == 1, r, rec0, n, lo, nv, ebase, a.list ? a.list + r0 : nullptr, rel != from, s_val,
