@@ -31,8 +31,8 @@ size_t part_lds(int npe, int W, int64_t elems, uint32_t nb_pad) {
 
 bool plan_bucket_map(int64_t n_elem, int64_t n_slots, int32_t n_vert, int K, int full, BkPlan* p) {
     if (n_slots < 1 || n_elem < 1 || n_vert < 1) return false;
-    // rows much longer than any mesh's go to the sorts: the networks take up
-    // to 32 (node) and 64 (element) values (tetrahedra average 24 elements)
+    // rows much longer than any mesh's go to the sorts: the networks take 32 values at
+    // a time (tetrahedra average 24 elements)
     if (n_slots > (int64_t)BK_MAX_DEGREE * n_vert) return false;
     p->n_elem = n_elem;
     p->n_slots = n_slots;
@@ -116,6 +116,7 @@ void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, 
     // tiles: large ones once they occupy every CU
     const int64_t big = with_type(etype, [](auto et) { return (int64_t)tile_elems<decltype(et)::value>(true); });
     p->large_tile = n_elem >= big * BK_CUS && part_lds(npe, p->W, big, p->mp.nb_pad) <= (size_t)BK_LDS;
+    if (!p->large_tile && n_elem >= big * BK_CUS && p->mp.n_bucket > BK_SMALL_TILE_MOST) return;
     const int64_t te = p->large_tile ? big : BK_SMALL_BLOCK;
     if (part_lds(npe, p->W, te, p->mp.nb_pad) > (size_t)BK_LDS) return;
     plan_bucket_layout(te, npe, limit, p);

@@ -25,6 +25,12 @@ constexpr int BK_LEAST_RECORDS = 384;  // fewest records a bucket of a small mes
 // 228.)
 constexpr int BK_FULL = 92, BK_FULL_PYRAMID = 56, BK_FULL_MIXED = 45;
 constexpr int bk_full(int32_t etype) { return etype == MESH_PYRAMID5 ? BK_FULL_PYRAMID : BK_FULL; }
+// Most buckets of a mesh that would fill the GPU with large tiles but has too many
+// buckets for their LDS.  Small tiles read and write ten bytes of counts per tile
+// and bucket: 165^3 hexahedra and wedges of 180 x 180 x 90 (6649 and 6656 buckets)
+// take 1702 and 1359 us, by sorting 1898 and 1534; 170^3 and 190 x 190 x 95 (7670)
+// 2052 and 2602, by sorting 2063 and 1787; 176^3 (8191) 3490, by sorting 2277.
+constexpr uint32_t BK_SMALL_TILE_MOST = 6656;
 constexpr int BK_HIST_BLOCKS = 512;    // blocks of bk_hist aimed at
 
 // Records and vertices a bucket may hold (BkShape).

@@ -521,9 +521,10 @@ __global__ __launch_bounds__(BLOCK) void bk_part_kernel(const int32_t* __restric
 }
 
 // The tile shapes: threads x elements per thread.  A large tile fills most of
-// a CU's LDS (records and their bucket numbers, 64 KB at least left over for
-// two words per bucket at the most buckets a plan asks for); a small mesh
-// takes small tiles, so that its few elements still spread over the CUs.
+// a CU's LDS (records and their bucket numbers; what is left, 34 KB for
+// triangles' three words and 50 KB for hexahedra's four, holds two words per
+// bucket and so bounds their number: 4320 and 6624).  Small tiles spread a small
+// mesh's elements over the CUs, and take what has more buckets than that.
 template <int ET>
 struct BkTile;
 template <> struct BkTile<TRI3> { static constexpr int BLOCK = 1024, EPT = 3; };

@@ -104,3 +104,31 @@ def test_scattered_mixed_mesh_vs_sort(n_vert, n_elem):
     conn, types = np.asarray(m.conn).ravel(), np.asarray(m.etypes)
     print(f"[irregular] mixed n_elem={n_elem} n_vert={n_vert}", flush=True)
     _equal(_mixed(conn, types, n_vert, None), _mixed(conn, types, n_vert, SORTED), n_elem)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,buckets", [(170, True), (180, True), (200, False)], ids=["large_tiles", "small_tiles", "sorts"])
+def test_too_many_buckets_for_small_tiles_are_left_to_the_sorts(n, buckets):
+    """Wedges of an n x n x n / 2 lattice's counts: which pipeline they take
+    shows in the names of its launches (the ids do not matter to the choice)."""
+    import torch
+
+    import paper_1604_04689_amd as nb
+    from paper_1604_04689_amd import binding
+    n_elem, n_vert = 2 * (n - 1) ** 2 * (n // 2), n * n * (n // 2 + 1)
+    print(f"[irregular] wedges n_elem={n_elem} n_vert={n_vert}", flush=True)
+    first = torch.arange(n_elem, dtype=torch.int32, device="cuda:0") % (n_vert // 6) * 6
+    conn = first[:, None] + torch.arange(6, dtype=torch.int32, device="cuda:0")
+    b = nb.NeighborBuild("both", n_elem, 4, n_vert, "cuda:0")
+    binding.timing_read()
+    binding.timing_enable(True)
+    try:
+        b.launch(conn)
+        torch.cuda.synchronize()
+    finally:
+        binding.timing_enable(False)
+    names = set(binding.timing_read())
+    (rp, cols), (erp, ecols) = b.result()
+    assert ("bucket_rows" in names) == buckets, names
+    used = n_vert // 6 * 6
+    assert cols.numel() == 3 * used and ecols.numel() == 6 * n_elem and int(erp[used]) == 6 * n_elem
