@@ -315,10 +315,14 @@ typedef struct {
  *   cols         device int32 [cols_capacity]; entries are LOCAL vertex ids
  * The slice row_ptr[vert_off .. vert_off + n_vert] - row_ptr[vert_off] with its
  * cols equals mesh_node_neighbors on that mesh alone.  Keys carry the global
- * vertex vert_off + u.  A record inconsistent with total_pairs, total_vert
- * or its own size (a key or vertex range outside the batch, an unknown type)
- * raises MESH_ERR_INDEX_RANGE on the device, and its pairs are dropped;
- * conn itself must cover every record (not checkable here). */
+ * vertex vert_off + u.  A record inconsistent with total_pairs, total_slots,
+ * total_vert, max_vert or its own size (a key, slot or vertex range outside the
+ * batch, more vertices than max_vert, an unknown type), or whose slot or vertex
+ * range starts before that of an earlier record ends, raises
+ * MESH_ERR_INDEX_RANGE on the device, and its pairs are dropped (where the
+ * pipeline that the options name does not need a field, a record that is wrong
+ * only there may pass); conn itself must cover every record (not checkable
+ * here). */
 mesh_status mesh_batch_node_neighbors_query(int32_t n_mesh, int64_t total_pairs, int64_t total_slots,
                                             int32_t total_vert, int32_t max_vert, const mesh_options* opts,
                                             size_t* workspace_bytes, int64_t* cols_capacity);

@@ -142,9 +142,10 @@ __device__ __forceinline__ uint32_t bkb_word_pairs(const BkMesh& e) {
     return (uint32_t)(((uint64_t)nodes_per_elem(e.etype) * (uint64_t)e.n_elem * (uint32_t)e.W + 8) / 2);
 }
 
-// A record is good when it fits the batch's totals and starts no earlier than
-// the records before it end.  A record that is not is reported and left out,
-// its rows empty.  One block, bound by its instructions and barriers (32-bit
+// A record is good when it fits the batch's totals and its vertices and slots
+// start no earlier than those of the records before it end.  (Where its pairs
+// start does not matter here: their number bounds the records' room.)  A record
+// that is not is reported and left out, its rows empty.  One block, bound by its instructions and barriers (32-bit
 // sums over DPP, the plan keeps every total below 2^32: 12 us for 512 meshes,
 // 84 us in 64 bits).
 __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
@@ -153,9 +154,11 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
     if (tid < (int)(HEADER_BYTES / 4)) a.hdr[tid] = 0;
     auto add = [](uint32_t x, uint32_t y) { return x + y; };
     auto most = [](uint32_t x, uint32_t y) { return max(x, y); };
-    uint32_t end[3] = {}, used[1] = {};  // ends so far: vertices, slots, pairs of any record; vertices of good ones
+    auto add_up_to = [](uint32_t x, uint32_t y) { return x + y < x ? UINT32_MAX : x + y; };
+    uint32_t end[2] = {}, used[1] = {};  // ends so far: vertices and slots of any record; vertices of good ones
+    uint32_t pairs[1] = {};              // pairs of any record so far, at most 2^32 - 1
     uint32_t sum[5] = {};                // buckets, tiles, blocks of bkb_scan, cells, word pairs
-    uint32_t mine[2] = {};               // slots and pairs of this thread's good records
+    uint32_t mine[1] = {};               // slots of this thread's good records
     bool bad = false;
     for (int64_t m0 = 0; m0 <= a.n_mesh; m0 += BKB_SETUP) {
         const int64_t i = m0 + tid;
@@ -166,19 +169,17 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
         bool good = in && npe > 0 && sg.n_elem >= 0 && sg.n_elem <= INT32_MAX && sg.n_vert >= 0 &&
                     sg.n_vert <= a.max_vert && sg.vert_off >= 0 && (int64_t)sg.vert_off + sg.n_vert <= a.total_vert &&
                     sg.slot_off >= 0 && sg.slot_off <= a.total_slots && sg.slot_off + npe * sg.n_elem <= a.total_slots &&
-                    sg.pair_off >= 0 && sg.pair_off <= a.total_pairs && sg.pair_off + ppe * sg.n_elem <= a.total_pairs;
+                    ppe * sg.n_elem <= a.total_pairs;
         const uint32_t vert = good ? (uint32_t)sg.vert_off : 0u, slot = good ? (uint32_t)sg.slot_off : 0u,
-                       pair = good ? (uint32_t)sg.pair_off : 0u, nv = good ? (uint32_t)sg.n_vert : 0u,
+                       nv = good ? (uint32_t)sg.n_vert : 0u,
                        ne = good ? (uint32_t)sg.n_elem : 0u;
-        uint32_t at[3] = {vert + nv, slot + npe * ne, pair + ppe * ne};
+        uint32_t at[2] = {vert + nv, slot + npe * ne}, before[1] = {(uint32_t)ppe * ne};
         bkb_block_scan(at, end, s_w, most);
-        good = good && vert >= at[0] && slot >= at[1] && pair >= at[2];
+        bkb_block_scan(before, pairs, s_w, add_up_to);
+        good = good && vert >= at[0] && slot >= at[1] && (int64_t)before[0] + ppe * ne <= a.total_pairs;
         uint32_t from[1] = {good ? vert + nv : 0u};
         bkb_block_scan(from, used, s_w, most);
-        if (good) {
-            mine[0] += npe * ne;
-            mine[1] += ppe * ne;
-        }
+        if (good) mine[0] += npe * ne;
         bad |= (in && !good) || (good && nv == 0 && ne > 0);
         // the vertices before it that no record covers, and the mesh; after the last one the vertices left
         const uint32_t gap = good ? vert - from[0] : tail ? (uint32_t)a.total_vert - from[0] : 0u;
@@ -207,14 +208,14 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
             put(2 * i + 1, mesh);
         }
     }
-    uint32_t all[2] = {};
+    uint32_t all[1] = {};
     bkb_block_scan(mine, all, s_w, add);
     bad = __syncthreads_or(bad);
     if (tid == 0) {
         a.hdr[HDR_BKB_BUCKETS] = sum[0];
         a.hdr[HDR_BKB_TILES] = sum[1];
         a.hdr[HDR_BKB_SCANS] = sum[2];
-        if (bad || all[0] != (uint32_t)a.total_slots || all[1] != (uint32_t)a.total_pairs) a.hdr[HDR_ERR] = ERR_INDEX_RANGE;
+        if (bad || all[0] != (uint32_t)a.total_slots) a.hdr[HDR_ERR] = ERR_INDEX_RANGE;
     }
 }
 

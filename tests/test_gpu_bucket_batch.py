@@ -154,3 +154,31 @@ def test_batch_buckets_leave_out_bad_records():
             assert not deg[a:z].any(), field
             keep = np.concatenate([w_cols[:w_rp[a]], w_cols[w_rp[z]:]])
             assert np.array_equal(cols[:len(keep)], keep), field
+
+
+@pytest.mark.gpu
+def test_batch_buckets_need_no_pair_offsets():
+    """Only pipelines that sort pairs read pair_off: as in the sort of the
+    elements, a batch whose records leave it out is built, and one of more
+    pairs than the batch is said to have is not."""
+    import torch
+
+    import paper_1604_04689_amd as nb
+    meshes = [grid(mg.tri_grid(40, "main", 1)), grid(mg.kuhn_tet_grid(6, 2)), grid(mg.hex_grid(8, 3))] * 5
+    conn = torch.as_tensor(np.concatenate([c.ravel() for c, _, _ in meshes]).astype(np.int32)).to("cuda:0")
+    want = _build(meshes, "both", SORTED)[1]
+    for options in (None, SORTED):
+        b = nb.BatchBuild("both", [(len(c), et, v) for c, et, v in meshes], "cuda:0", options=options)
+        seg = b.seg_host.copy()
+        seg["pair_off"] = 0
+        b.segs[:seg.nbytes].copy_(torch.as_tensor(seg.view("u1")).to("cuda:0"))
+        b.launch(conn)
+        got = [x.cpu().numpy() for rel in b.result() for x in rel]
+        for g, w in zip(got, want):
+            assert np.array_equal(g, w), options
+    b = nb.BatchBuild("both", [(len(c), et, v) for c, et, v in meshes], "cuda:0")
+    b.totals["pairs"] -= 2
+    b.launch(conn)
+    with pytest.raises(nb.MeshError) as e:
+        b.result()
+    assert e.value.status == nb.Status.INDEX_RANGE
