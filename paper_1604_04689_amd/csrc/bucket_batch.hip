@@ -166,7 +166,7 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
         mesh_segment sg{};
         if (in) sg = a.segs[i];
         const int npe = nodes_per_elem(sg.etype), ppe = 2 * edges_per_elem(sg.etype);
-        bool good = in && npe > 0 && sg.n_elem >= 0 && sg.n_elem <= INT32_MAX && sg.n_vert >= 0 &&
+        bool good = in && (npe > 0 || sg.n_elem == 0) && sg.n_elem >= 0 && sg.n_elem <= INT32_MAX && sg.n_vert >= 0 &&
                     sg.n_vert <= a.max_vert && sg.vert_off >= 0 && (int64_t)sg.vert_off + sg.n_vert <= a.total_vert &&
                     sg.slot_off >= 0 && sg.slot_off <= a.total_slots && sg.slot_off + npe * sg.n_elem <= a.total_slots &&
                     ppe * sg.n_elem <= a.total_pairs;
@@ -185,7 +185,8 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_setup_kernel(SetupArgs a) {
         const uint32_t gap = good ? vert - from[0] : tail ? (uint32_t)a.total_vert - from[0] : 0u;
         BkMesh hole{}, mesh{};
         if (gap) hole = bkb_entry(a, gap, 0, TRI3, (int32_t)from[0], 0);
-        if (good) mesh = bkb_entry(a, nv, nv ? ne : 0u, sg.etype, sg.vert_off, sg.conn_off);
+        // (the type of a mesh without elements may be anything)
+        if (good) mesh = bkb_entry(a, nv, nv ? ne : 0u, npe > 0 ? sg.etype : (int32_t)TRI3, sg.vert_off, sg.conn_off);
         const uint32_t scans = ceil_div32(hole.mp.n_bucket, BKS_COLS);
         uint32_t o[5] = {hole.mp.n_bucket + mesh.mp.n_bucket, mesh.n_tiles, scans + ceil_div32(mesh.mp.n_bucket, BKS_COLS),
                          mesh.n_tiles * mesh.mp.nb_pad, bkb_word_pairs(hole) + bkb_word_pairs(mesh)};

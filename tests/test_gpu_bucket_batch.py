@@ -182,3 +182,23 @@ def test_batch_buckets_need_no_pair_offsets():
     with pytest.raises(nb.MeshError) as e:
         b.result()
     assert e.value.status == nb.Status.INDEX_RANGE
+
+
+@pytest.mark.gpu
+def test_batch_buckets_take_any_type_of_an_empty_mesh():
+    import torch
+
+    import paper_1604_04689_amd as nb
+    empty = np.zeros((0, 3), np.int32)
+    meshes = [(empty, 0, 7), grid(mg.tri_grid(40, "main", 1)), (empty, 0, 900), grid(mg.hex_grid(8, 3)), (empty, 0, 0)]
+    conn = torch.as_tensor(np.concatenate([c.ravel() for c, _, _ in meshes]).astype(np.int32)).to("cuda:0")
+    want = _build(meshes, "both", SORTED)[1]
+    for options in (SORTED, None):
+        b = nb.BatchBuild("both", [(len(c), et, v) for c, et, v in meshes], "cuda:0", options=options)
+        seg = b.seg_host.copy()
+        seg["etype"][[0, 2, 4]] = (99, -5, 6)
+        b.segs[:seg.nbytes].copy_(torch.as_tensor(seg.view("u1")).to("cuda:0"))
+        b.launch(conn)
+        got = [x.cpu().numpy() for rel in b.result() for x in rel]
+        for g, w in zip(got, want):
+            assert np.array_equal(g, w), options
