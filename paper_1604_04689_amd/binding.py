@@ -210,8 +210,11 @@ def _sizes(workspace, stream, device, *row_ptrs):
     94 us with those and 65 us so)."""
     import torch
 
-    with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(device)):
-        err, *sizes = torch.cat([workspace[:4].view(torch.int32), *[r[-1:] for r in row_ptrs]]).tolist()
+    try:
+        with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(device)):
+            err, *sizes = torch.cat([workspace[:4].view(torch.int32), *[r[-1:] for r in row_ptrs]]).tolist()
+    except RuntimeError as e:  # of this call or of one before it on the device
+        raise MeshError(Status.HIP, "mesh_check") from e
     for bit, status in _ERROR_BITS:
         if err & bit:
             raise MeshError(status, "mesh_check")
