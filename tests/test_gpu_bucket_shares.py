@@ -163,3 +163,55 @@ def test_mixed_mesh_with_shared_buckets(n_elem, n_vert, power):
         r = b.result()
         got.append([*r[0], *r[1]])
     _equal(got[1], got[0], "mixed")
+
+
+def _stretch(m, times):
+    """A mesh over `times` as many vertices as its elements use, those first."""
+    return m.conn, m.etype, times * m.n_vert
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mesh", [
+    # records of a used bucket, for what its block holds: both relations, and the element relation alone
+    lambda mg: _stretch(mg.kuhn_tet_grid(50, 2), 3),        # 8800 for 5952, 17,600 for 14,848
+    lambda mg: _stretch(mg.tri_grid(700, "coin", 3), 10),   # 8200 for 7680
+    lambda mg: _stretch(mg.tri_grid(120, "main", 4), 9),    # small buckets: 3800 for 3072
+    lambda mg: _stretch(mg.pyramid_grid(20, 5), 6),
+    lambda mg: _stretch(mg.hex_grid(60, 6), 8),
+], ids=["tets", "triangles", "few_triangles", "pyramids", "hexahedra"])
+def test_elements_on_the_first_vertices_only(mesh):
+    """The corners of a quadratic mesh numbered first, or a part of a mesh in
+    the numbering of the whole: the used buckets hold more than was planned."""
+    from paper_1604_04689_amd import meshgen as mg
+    conn, etype, n_vert = mesh(mg)
+    _check(conn, etype, n_vert, "first vertices")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [501, 20001])
+def test_overlapping_elements_touch_nothing_outside(n):
+    """Offsets that go back and forth ask for more (vertex, element) pairs than
+    there are ids: reported, and the words around the outputs and behind the
+    workspace stay as they were."""
+    import torch
+
+    import paper_1604_04689_amd as nb
+    off = np.where(np.arange(n + 1) % 2 == 0, 0, 8).astype(np.int32)
+    conn = (np.arange(n * 2) % 9000).astype(np.int32)
+    b = nb.MixedBuild(n, len(conn), 24 * n, 9000, "cuda:0")
+    guard, outs = 1024, {}
+    for k in ("row_ptr", "cols", "elem_row_ptr", "elem_cols"):
+        t = getattr(b, k)
+        outs[k] = torch.full((t.numel() + 2 * guard,), 7, dtype=torch.int32, device="cuda:0")
+        setattr(b, k, outs[k][guard:-guard])
+    raw = torch.full((b.ws_bytes + 8192,), 90, dtype=torch.uint8, device="cuda:0")
+    pad = (-raw.data_ptr()) % 256
+    b.workspace = raw[pad:pad + b.ws_bytes]
+    print(f"[shares] overlapping n_elem={n}", flush=True)
+    b.launch(*[torch.as_tensor(x).to("cuda:0") for x in (conn, off, np.full(n, 2, np.uint8))])
+    with pytest.raises(nb.MeshError) as e:
+        b.result()
+    assert e.value.status == nb.Status.INDEX_RANGE
+    for k, t in outs.items():
+        assert (t[:guard] == 7).all() and (t[-guard:] == 7).all(), k
+    assert (raw[:pad] == 90).all() and (raw[pad + b.ws_bytes:] == 90).all()
