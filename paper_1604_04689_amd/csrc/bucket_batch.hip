@@ -304,7 +304,7 @@ __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __rest
                                                            const uint32_t* __restrict__ scan0, int entries,
                                                            uint32_t* __restrict__ cells, uint32_t* __restrict__ totals,
                                                            uint32_t* __restrict__ more, BkbCaps cap,
-                                                           uint32_t* __restrict__ bmesh, uint64_t* __restrict__ lookback,
+                                                           uint32_t* __restrict__ bmesh, BkLookback lookback,
                                                            uint32_t* __restrict__ repeats, uint32_t* hdr) {
     __shared__ uint32_t s_sum[BKB_ROWS][BKS_COLS];
     const int tid = threadIdx.x;
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __rest
         more[at] = shares - 1;
         if (shares > 1) atomicOr(&hdr[HDR_BKB_SHARED], 1u);
         bmesh[at] = (uint32_t)k;
-        lookback[at] = 0;  // bkb_rows'
+        lookback.clear(at);
         repeats[at] = 0;   // counted by bkb_part
     }
     each([&](const uint32_t(&v)[BKB_AHEAD], const uint32_t(&t)[BKB_AHEAD]) {
@@ -404,7 +404,7 @@ __device__ __forceinline__ uint32_t bkb_sums(uint32_t* __restrict__ a, uint32_t 
     return all;
 }
 __global__ __launch_bounds__(BKB_SETUP) void bkb_starts_kernel(uint32_t* __restrict__ starts, uint32_t* __restrict__ units,
-                                                              uint64_t* __restrict__ lookback, uint32_t* hdr) {
+                                                              BkLookback lookback, uint32_t* hdr) {
     __shared__ uint32_t s_w[1][BKB_SETUP_WAVES];
     const uint32_t n = hdr[HDR_BKB_BUCKETS];
     const bool shared = hdr[HDR_BKB_SHARED] != 0;
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(BKB_SETUP) void bkb_starts_kernel(uint32_t* __restr
     uint32_t all = n;
     if (shared) {
         all = bkb_sums(units, n, true, s_w);
-        for (uint32_t u = n + threadIdx.x; u < all; u += BKB_SETUP) lookback[u] = 0;
+        for (uint32_t u = n + threadIdx.x; u < all; u += BKB_SETUP) lookback.clear(u);
     }
     if (threadIdx.x == 0) hdr[HDR_BK_UNITS] = all;
 }
@@ -519,7 +519,7 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
     take(&p->off_starts, ((size_t)p->bucket_most + 1) * 4);
     take(&p->off_units, ((size_t)p->bucket_most + 1) * 4);
     take(&p->off_rep, (size_t)p->bucket_most * 4);
-    take(&p->off_lb, (size_t)p->unit_most * 8);
+    take(&p->off_lb, BkLookback::bytes(p->unit_most));
     take(&p->off_rec, (size_t)p->word_most * 4);
     take(&p->off_cells, (size_t)p->cell_most * 4);
     // the lists of shared buckets over the counts, which are done with by then, if they fit
@@ -562,7 +562,7 @@ hipError_t run_batch_buckets(const BkBatchPlan& p, const int32_t* conn, const me
     uint32_t* starts = (uint32_t*)(w + p.off_starts);
     uint32_t* units = (uint32_t*)(w + p.off_units);
     uint32_t* repeats = (uint32_t*)(w + p.off_rep);
-    uint64_t* lookback = (uint64_t*)(w + p.off_lb);
+    const BkLookback lookback = BkLookback::at(w + p.off_lb, p.unit_most);
     const BkbCaps caps{(uint32_t)bk_size(2, p.large).cap, (uint32_t)bk_size(3, p.large).cap, (uint32_t)bk_size(4, p.large).cap};
     const auto grid = [&](int64_t per_cu) {  // a multiple of the XCDs
         return dim3((unsigned)tmin<int64_t>(ceil_div(p.tile_most, (int64_t)BK_XCDS) * BK_XCDS, per_cu * BK_CUS));

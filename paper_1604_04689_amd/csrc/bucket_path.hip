@@ -92,7 +92,8 @@ void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* 
     p->off_rep = off;
     off += align_up((size_t)m.n_bucket * sizeof(uint32_t));
     p->off_lb = off;
-    off += align_up((size_t)bk_unit_most(m.n_bucket, p->n_elem * most_npe, bk_size(p->K, p->large).cap) * sizeof(uint64_t));
+    p->unit_most = bk_unit_most(m.n_bucket, p->n_elem * most_npe, bk_size(p->K, p->large).cap);
+    off += align_up(BkLookback::bytes(p->unit_most));
     p->off_rec = off;
     off += align_up(((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
     p->off_btot = p->off_list = off;
@@ -148,7 +149,8 @@ hipError_t launch_tiles(const BkPlan& p, const int32_t* conn, char* w, hipStream
         e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)ceil_div(p.mp.n_bucket, BKS_COLS)), dim3(BKS_BLOCK), s,
                    btot, p.hist_blocks, p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags,
                    (uint64_t*)(w + p.off_scan), (uint32_t*)(w + p.off_starts), (uint32_t*)(w + p.off_units),
-                   (uint32_t)bk_size(p.K, p.large).cap, (uint32_t)p.n_slots, (uint64_t*)(w + p.off_lb), (uint32_t*)(w + p.off_rep), hdr);
+                   (uint32_t)bk_size(p.K, p.large).cap, (uint32_t)p.n_slots,
+                   BkLookback::at(w + p.off_lb, p.unit_most), (uint32_t*)(w + p.off_rep), hdr);
     if (e != hipSuccess) return e;
     if (p.K == 0)
         return p.W == 1 ? launch_part<ET, 0, 1, LT>(p, conn, w, s) : launch_part<ET, 0, 2, LT>(p, conn, w, s);

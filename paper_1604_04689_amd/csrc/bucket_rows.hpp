@@ -345,7 +345,7 @@ struct BkRowsArgs {
     const uint32_t* starts;
     const uint32_t* units;    // first unit per bucket
     const uint32_t* repeats;  // per bucket: records whose pair an earlier record of the element has
-    uint64_t* lookback;
+    BkLookback lookback;
     uint32_t* list;  // a word per record for those of shared buckets (null: no room)
     uint32_t* hdr;
     int32_t* nrp;    // node CSR (null: not wanted)
@@ -473,14 +473,15 @@ struct BkUnit {
     uint32_t unit, bucket, share, shares;
     bool last;  // of all
 };
-// The unit's node entries go to the look-back word, the sum of the earlier
-// units' comes back (every thread).
-__device__ __forceinline__ void bk_publish(const BkRowsArgs& a, uint32_t unit, uint64_t mine) {
-    if (bk_tid() == 0) lb_store(a.lookback + unit, (unit == 0 ? LB_INC : LB_AGG) | mine);
+// The unit's entries go to its look-back word, the sum of the earlier units'
+// comes back (every thread).
+__device__ __forceinline__ void bk_publish(uint64_t* lookback, uint32_t unit, uint64_t mine) {
+    if (bk_tid() == 0) lb_store(lookback + unit, (unit == 0 ? LB_INC : LB_AGG) | mine);
 }
-__device__ __forceinline__ uint64_t bk_before(const BkRowsArgs& a, uint32_t unit, uint64_t mine, uint64_t* s_base) {
+__device__ __forceinline__ uint64_t bk_before(const BkRowsArgs& a, uint64_t* lookback, uint32_t unit, uint64_t mine,
+                                              uint64_t* s_base) {
     if (bk_tid() < WAVE) {
-        const uint64_t p = wave_lookback_prefix(a.lookback, unit, mine, a.hdr + HDR_ERR, a.hdr + HDR_BK_PROGRESS);
+        const uint64_t p = wave_lookback_prefix(lookback, unit, mine, a.hdr + HDR_ERR, a.hdr + HDR_BK_PROGRESS);
         if (bk_tid() == 0) *s_base = p;
     }
     __syncthreads();
@@ -598,12 +599,12 @@ __device__ __forceinline__ void bk_sort_range(uint32_t* s_val, const uint32_t* s
 
 // Windows [wa, wb) of one row (vertex v of the bucket) beyond the LDS, from the
 // records that bk_each_record takes, each its ids in a bit map of `words` words at s_map.  With write, they go to cols from
-// `at` on (as far as cap lets); for elements, which have no repeats where wa >
-// 0, `at` is where the whole row starts.  Returns their number.
+// `at` on (as far as cap lets); with row_start, `at` is where the whole row starts
+// (of elements without repeats).  Returns their number.
 template <int K, int W, int BLOCK>
 __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint32_t* rec, const uint32_t* list,
                                                 uint32_t n, uint32_t lo, int v,
-                                                uint32_t wa, uint32_t wb, bool elements, uint32_t* s_map, uint32_t words,
+                                                uint32_t wa, uint32_t wb, bool elements, bool row_start, uint32_t* s_map, uint32_t words,
                                                 uint32_t* s_tmp, int* turn, bool write, int32_t* cols, uint64_t at,
                                                 int64_t cap, bool* full) {
     const int tid = bk_tid();
@@ -639,7 +640,7 @@ __device__ __forceinline__ uint32_t bk_huge_row(const BkRowsArgs& a, const uint3
         uint32_t c = 0;
         for (uint32_t i = lane; i < per; i += WAVE) c += (uint32_t)__popc(map[i]);
         uint32_t total, skip = 0;
-        if (elements && w == wa && wa > 0) bk_block_sum<BLOCK>(below, s_tmp, turn, &skip);
+        if (row_start && w == wa && wa > 0) bk_block_sum<BLOCK>(below, s_tmp, turn, &skip);
         at += skip;
         uint32_t place = bk_block_sum<BLOCK>(c, s_tmp, turn, &total);
         place = (uint32_t)__builtin_amdgcn_readfirstlane((int)place);
@@ -715,14 +716,15 @@ __device__ __forceinline__ int bk_first_from(const uint32_t* s_start, int nv, ui
 
 // One relation of any unit, from its bucket's records in memory: ranges of
 // vertices whose records fit the LDS.  elements: the element rows, the bucket's
-// starting at `ebase`; else the node rows, which are counted first (a unit in
-// one range keeps them in the LDS meanwhile).  Share i takes the vertices whose
+// starting at `ebase`; else the node rows.  Those, and the element rows of a
+// share where the bucket has repeats, are counted first (a unit in one range
+// keeps them in the LDS meanwhile).  Share i takes the vertices whose
 // records start in the i-th part of the bucket's, and lists them by vertex (at
 // `list`, if there is room), so that a range reads only its own.  `again`: the
 // unit has done its node rows here, and the counts and the list stand.  Every
 // thread of the block calls it.
 template <int K, int W, bool LARGE>
-__device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, BkUnit u, int64_t rec0, uint32_t n,
+__device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, bool repeats, const BkUnit& u, int64_t rec0, uint32_t n,
                                           uint32_t lo, int nv, uint64_t ebase, uint32_t* list, bool again,
                                           uint32_t* s_val, uint32_t* s_start, uint32_t* s_cnt, uint16_t* s_pos,
                                           uint32_t* s_tmp, int* turn, uint64_t* s_base) {
@@ -755,7 +757,7 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
     // has its records listed
     auto window = [&](int v, bool end) BK_INLINE {
         const uint32_t first = s_start[v] / part, shares = (s_start[v + 1] - 1) / part + 1 - first;
-        if (shares < 4) return u.shares > 1 && first != u.share ? windows : end ? windows : 0u;
+        if (shares < 4) return first != u.share ? windows : end ? windows : 0u;
         return (uint32_t)((uint64_t)windows * (u.share - first + (end ? 1 : 0)) / shares);
     };
     // (the list takes one pass over all records: not for a share of one range, or of a
@@ -775,10 +777,10 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
     auto own = [&](int va) BK_INLINE { return list && va >= v0 ? list + s_start[va] : nullptr; };
     auto records = [&](int va, int vb) BK_INLINE { return list && va >= v0 ? s_start[vb] - s_start[va] : n; };
     const bool single = !head && (v0 == v1 || bk_range_end(s_start, v0, v1, most) == v1);
+    const bool counted = !elements || (repeats && u.shares > 1);
     uint64_t base = ebase, run = 0;
-    if (elements) base += s_start[head ? v0 - 1 : v0];
-    else base = 0;
-    for (int phase = elements ? 1 : 0; phase < 2; ++phase) {  // 0: count, 1: write
+    if (!counted && u.shares > 1) base += s_start[head ? v0 - 1 : v0];
+    for (int phase = counted ? 0 : 1; phase < 2; ++phase) {  // 0: count, 1: write
         run = 0;
         for (int va = head ? v0 - 1 : v0; va < v1;) {
             const int vb = va < v0 ? va : bk_range_end(s_start, va, v1, most);
@@ -786,13 +788,13 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
             if (vb == va) {
                 if (phase == 1 && va >= v0 && tid == 0) rp[lo + va] = (int32_t)at;
                 run += bk_huge_row<K, W, BLOCK>(a, rec, own(va), records(va, va + 1), lo, va, window(va, false),
-                                                window(va, true), elements, s_val, (uint32_t)S::POOL, s_tmp, turn, phase == 1, cols, at, cap, &full);
+                                                window(va, true), elements, !counted, s_val, (uint32_t)S::POOL, s_tmp, turn, phase == 1, cols, at, cap, &full);
                 ++va;
-                if (elements && u.shares > 1) run = ebase + s_start[va] - base;  // (its end, if here; else nothing follows)
+                if (!counted && u.shares > 1) run = ebase + s_start[va] - base;  // (its end, if here; else nothing follows)
                 continue;
             }
             const uint32_t s0 = s_start[va];
-            if (phase == 0 || elements || !single) {
+            if (phase == 0 || !counted || !single) {
                 for (int v = va + tid; v < vb; v += BLOCK) s_cnt[v] = 0;
                 __syncthreads();
                 bk_each_record<W, BLOCK>(a, rec, own(va), records(va, vb), [&](const uint32_t (&r)[W], uint32_t, auto) BK_INLINE {
@@ -829,8 +831,11 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, Bk
             va = vb;
         }
         if (phase == 0) {
-            bk_publish(a, u.unit, run);
-            base = bk_before(a, u.unit, run, s_base);
+            uint64_t* const lookback = elements ? a.lookback.elems + (u.unit - u.share) : a.lookback.nodes;
+            const uint32_t place = elements ? u.share : u.unit;
+            bk_publish(lookback, place, run);
+            base = bk_before(a, lookback, place, run, s_base);
+            if (elements) base += ebase;
             __syncthreads();
         }
     }
@@ -986,11 +991,11 @@ __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u,
         if (wide) rows(std::integral_constant<int, (int)BK_NET_MAX>{});
         else rows(std::integral_constant<int, 16>{});
         if (total >= STUCK) return 0;  // a row beyond the networks
-        bk_publish(a, u.unit, total);
+        bk_publish(a.lookback.nodes, u.unit, total);
     }
     bool full = false;
     auto nodes_out = [&]() BK_INLINE {
-        const uint64_t base = bk_before(a, u.unit, total, s_base);
+        const uint64_t base = bk_before(a, a.lookback.nodes, u.unit, total, s_base);
         for (int v = tid; v < nv; v += BLOCK) a.nrp[lo + v] = (int32_t)(base + s_cnt[v]);
         if (u.last && tid == 0) a.nrp[a.mp.n_vert] = (int32_t)(base + total);
         if ((int64_t)(base + total) > a.ncap) full = true;
@@ -1122,13 +1127,10 @@ __device__ __forceinline__ void bk_unit_rows(const BkRowsArgs& a, const BkUnit& 
         done = bk_rows_lds<K, W, LARGE>(a, u, rec0, n, lo, nv, odd, elem, repeats, ebase, s_val, s_start, s_cnt, s_tmp, &turn,
                                         s_base);
     const bool node_left = node && !(done & BK_NODE_DONE);
-    // (where the rows of a share start follows from the counts only without repeats: the last share takes all)
-    const bool elem_left = elem && !(done & BK_ELEM_DONE) && (!repeats || u.share + 1 == u.shares);
+    const bool elem_left = elem && !(done & BK_ELEM_DONE);
 #pragma unroll 1
     for (int rel = node_left ? 0 : 1, from = rel; rel < (elem_left ? 2 : 1); ++rel) {
-        BkUnit r = u;
-        if (rel == 1 && repeats) r.shares = 1;
-        bk_ranges<K, W, LARGE>(a, rel == 1, r, rec0, n, lo, nv, ebase, a.list ? a.list + r0 : nullptr, rel != from, s_val,
+        bk_ranges<K, W, LARGE>(a, rel == 1, repeats, u, rec0, n, lo, nv, ebase, a.list ? a.list + r0 : nullptr, rel != from, s_val,
                                s_start, s_cnt, s_pos, s_tmp, &turn, s_base);
     }
 }

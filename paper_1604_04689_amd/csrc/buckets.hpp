@@ -77,6 +77,15 @@ __host__ __device__ inline uint32_t bk_first_vertex(uint32_t bucket, uint32_t mu
 }
 __device__ __forceinline__ uint32_t bk_bucket(uint32_t v, uint32_t mul) { return __umulhi(v, mul); }
 
+// bk_rows' look-backs, a word per unit each: node entries, and, within a shared
+// bucket that has repeats (of a vertex in an element), element entries.
+struct BkLookback {
+    uint64_t *nodes, *elems;
+    __device__ __forceinline__ void clear(uint32_t unit) const { nodes[unit] = elems[unit] = 0; }
+    static size_t bytes(int64_t units) { return (size_t)units * 2 * sizeof(uint64_t); }
+    static BkLookback at(void* p, int64_t units) { return {(uint64_t*)p, (uint64_t*)p + units}; }
+};
+
 // Blocks that share a bucket of n records.  Up to cap of them fit one block's
 // LDS.  Beyond, every share reads all of the bucket's records (to count them by
 // vertex, and to pick its own), so their number is bounded: 128 blocks that
@@ -293,7 +302,7 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
                                                                   const uint32_t* __restrict__ flags,
                                                                   uint64_t* scan_lb, uint32_t* __restrict__ starts,
                                                                   uint32_t* __restrict__ units, uint32_t bucket_cap,
-                                                                  uint32_t rec_cap, uint64_t* __restrict__ lookback,
+                                                                  uint32_t rec_cap, BkLookback lookback,
                                                                   uint32_t* __restrict__ repeats, uint32_t* hdr) {
     __shared__ uint32_t s_sum[BKS_ROWS][BKS_COLS + 1];
     __shared__ uint32_t s_tot[BKS_COLS];
@@ -353,8 +362,8 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
             const uint32_t u = b + (uint32_t)(from >> 32);
             starts[b] = tmin((uint32_t)from, rec_cap);
             units[b] = u;
-            for (uint32_t i = 0; i <= more; ++i) lookback[u + i] = 0;  // bk_rows'
-            repeats[b] = 0;                                            // counted by bk_part
+            for (uint32_t i = 0; i <= more; ++i) lookback.clear(u + i);
+            repeats[b] = 0;  // counted by bk_part
             if (b + 1 == n_bucket) {
                 starts[n_bucket] = tmin((uint32_t)to, rec_cap);
                 units[n_bucket] = u + more + 1;

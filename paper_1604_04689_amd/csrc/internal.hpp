@@ -85,7 +85,7 @@ hipError_t run_elem(const ElemPlan& p, const int32_t* conn, int32_t* row_ptr, in
 struct ErowsPlan {
     int64_t n_entries = 0;    // upper bound of element-relation entries
     int slots = 0;            // candidate slots per entry (S)
-    int64_t n_tiles = 0;
+    int64_t n_tiles = 0, unit_most = 0;
     int64_t long_cap = 0;
     size_t off_lb = 0;        // count scan look-back words (cleared by the call's fill)
     int64_t lb_words = 0;     // their size in 32-bit words
@@ -166,7 +166,7 @@ struct BkPlan {
     int64_t n_elem = 0, n_slots = 0;
     int32_t etype = 0;
     BkMap mp;
-    int64_t n_tiles = 0;
+    int64_t n_tiles = 0, unit_most = 0;
     int R = 1;                // tiles per bk_hist block
     int hist_blocks = 0;
     size_t off_flags = 0, off_scan = 0, off_starts = 0, off_units = 0, off_rep = 0, off_lb = 0, off_btot = 0, off_within = 0,

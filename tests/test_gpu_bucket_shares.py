@@ -78,6 +78,17 @@ def test_hubs(n_vert, first, count, size):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n_vert,first,count,size", [(1_200_000, 0, 1, 60_000), (300_000, 0, 60, 3000),
+                                                     (700_000, 699_993, 7, 9000)])
+def test_hubs_with_repeated_ids(n_vert, first, count, size):
+    """The shares' element rows are then counted before they have a place."""
+    conn = hubs(n_vert, first, count, size, 200_000, size + 1)
+    conn[::97, 1] = conn[::97, 0]
+    conn[5::1001, 2] = conn[5::1001, 1]
+    _check(conn, 0, n_vert, f"{count} hubs of {size}, repeated ids")
+
+
+@pytest.mark.gpu
 def test_hubs_vs_oracle(oracle_mod):
     conn = hubs(50_000, 20_000, 40, 2500, 30_000, 4)
     want = [*oracle_mod.node_neighbors(conn, 0, 50_000), *oracle_mod.elem_neighbors(conn, 0, 50_000)]
