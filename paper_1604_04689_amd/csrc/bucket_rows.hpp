@@ -844,10 +844,10 @@ __device__ __forceinline__ void bk_ranges(const BkRowsArgs& a, bool elements, bo
 }
 
 // A bucket of at most CAP records over nv vertices, from registers and LDS.
-// Which relations are done: none where a node row is left to bk_ranges, with
-// nothing announced or written yet (a row of more than 64 distinct values, or a
-// second one of more than 32 among 64 rows), and no element rows where the bucket
-// has repeats (of a vertex in an element) and a row beyond the networks.
+// Which relations are done: no node rows where one is left to bk_ranges, with
+// nothing of them announced or written yet (a row of more than 64 distinct values,
+// or a second one of more than 32 among 64 rows), and no element rows where the
+// bucket has repeats (of a vertex in an element) and a row beyond the networks.
 constexpr int BK_NODE_DONE = 1, BK_ELEM_DONE = 2;
 template <int K, int W, bool LARGE>
 __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u, int64_t rec0, uint32_t n, uint32_t lo,
@@ -934,6 +934,7 @@ __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u,
     constexpr uint32_t STUCK = S::POOL + 1;
     static_assert(K * CAP <= S::POOL && (uint64_t)BLOCK * STUCK + S::POOL <= UINT32_MAX, "marks never cancel out");
     uint32_t total = 0;
+    bool stuck = false;
     if (K > 0 && node) {
         constexpr uint32_t MID_ROW = 512;
         auto rows = [&](auto most) BK_INLINE {  // rounds of up to `most` values
@@ -990,8 +991,8 @@ __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u,
         };
         if (wide) rows(std::integral_constant<int, (int)BK_NET_MAX>{});
         else rows(std::integral_constant<int, 16>{});
-        if (total >= STUCK) return 0;  // a row beyond the networks
-        bk_publish(a.lookback.nodes, u.unit, total);
+        stuck = total >= STUCK;  // a row beyond the networks
+        if (!stuck) bk_publish(a.lookback.nodes, u.unit, total);
     }
     bool full = false;
     auto nodes_out = [&]() BK_INLINE {
@@ -1005,7 +1006,7 @@ __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u,
     // rows that share no neighbours leave no room for the elements after them: they go
     // out first (500,000 vertices, 1 M random triangles: 284 us with the rows made again
     // from memory, 171 so)
-    const bool crowded = K > 0 && node && elem && total + n > (uint32_t)S::POOL;
+    const bool crowded = K > 0 && node && elem && !stuck && total + n > (uint32_t)S::POOL;
     if (K > 0 && crowded) {
         nodes_out();
         __syncthreads();
@@ -1086,11 +1087,11 @@ __device__ __forceinline__ int bk_rows_lds(const BkRowsArgs& a, const BkUnit& u,
     }
 
     // ---- node rows out
-    if (K > 0 && node && !crowded) nodes_out();
+    if (K > 0 && node && !crowded && !stuck) nodes_out();
     if (full) set_error(a.hdr + HDR_ERR, ERR_CAPACITY);
     // (records beyond the room there is, of an ill-formed mixed mesh, are missing)
     if (bad && !(odd & BK_BAD_ID)) set_error(a.hdr + HDR_ERR, ERR_INTERNAL);
-    return BK_NODE_DONE | (elem ? BK_ELEM_DONE : 0);
+    return (stuck ? 0 : BK_NODE_DONE) | (elem ? BK_ELEM_DONE : 0);
 }
 
 // Unit u, of a bucket of n records from rec0 on, the r0-th pair of all: both its
