@@ -25,15 +25,16 @@ constexpr int BKB_LDS = 78 * 1024;     // of a bkb_part tile: two blocks per CU
 constexpr int BKB_NB_MOST = 4096;      // most buckets of one mesh (two words each of that LDS)
 // Batches of many tiny meshes go to the sorts: every mesh has a tile and a
 // bucket of its own, about 60 ns (16,384 triangle meshes of 54 / 726 / 1350 /
-// 3174 slots: 735 / 1024 / 1133 / 1473 us against 245 / 829 / 1144 / 2417 us by
+// 3174 slots: 710 / 952 / 1069 / 1341 us against 249 / 826 / 1139 / 2417 us by
 // sorting).  Up to 2048 meshes the buckets' fewer launches make up for that
-// (2048 meshes of 54 slots: 132 against 177 us).
+// (2048 meshes of 54 slots: 124 against 185 us).
 constexpr int BKB_MESHES = 2048;
 constexpr int BKB_MESH_SLOTS = 1400;
 constexpr int BKB_TILE_LEAST = 512;    // fewest slots a tile is cut for
 constexpr int BKB_SETUP = 1024;
-// Most small buckets of a batch: 1.4 M slots took 77 us in small ones, 80 us in
-// large ones, which are not rounded up to whole rounds here.
+// Most small buckets of a batch: 1.6 M slots in 12 meshes took 80 us in small ones,
+// 86 us in large ones (which are not rounded up to whole rounds here), 110,000 in
+// 2048 meshes 123 and 141, 1.8 M in 180 meshes 103 and 95.
 constexpr int BKB_SMALL_MOST = 1024;
 
 constexpr int bkb_K(int32_t et) { return et == TRI3 || et == QUAD4 ? 2 : et == PYR5 ? 4 : 3; }

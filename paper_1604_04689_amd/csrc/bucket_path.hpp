@@ -8,21 +8,24 @@ namespace mnb {
 constexpr int BK_CUS = 256;            // CUs of the GPU
 constexpr int BK_MAX_DEGREE = 40;      // most elements per vertex, on average, of a mesh that takes buckets
 // Most small buckets of a mesh.  More of them run in several rounds, and large
-// ones have twice the threads to a bucket: 512 large buckets took 54 / 50 / 61 us
-// where 566 / 566 / 850 small ones took 57 / 55 / 71 us (hexahedra 55^3, their
+// ones have twice the threads to a bucket: 512 large buckets took 55 / 52 / 62 us
+// where 566 / 566 / 850 small ones took 60 / 56 / 72 us (hexahedra 55^3, their
 // node relation, 63^3); 512 half-empty large ones lose below (tetrahedra 32^3:
-// 54 us against 51 us in 334 small ones).
+// 56 us against 52 us in 334 small ones).
 constexpr int BK_SMALL_MOST = 448;
 constexpr int BK_LEAST_RECORDS = 384;  // fewest records a bucket of a small mesh is planned for
 // Records of a bucket, percent of what it holds, on average: a bucket with more
-// than it holds is finished from memory, and every later one waits for it.  The
+// than it holds is finished from memory, by several blocks (bk_shares), at two to
+// four times the cost of its records, and every later one waits for it.  The
 // vertices of most meshes of one type differ little.  A pyramid's apex has 6
 // elements where a corner of its base has 24, and labels with locality put
 // vertices of a kind side by side, so buckets of corners get 24 / 15 of the
-// average; in a hybrid mesh they get about twice the average.  (Local labels, us:
-// element relation of 90^3 pyramid cells 511 at 92 % and 315 at 56 %; hybrid
-// mesh of 4 M ids 472 at 80 % and 203 at 45 %, where shuffled ones take 225 and
-// 228.)
+// average; in a hybrid mesh they get about twice the average.  These two are the shares of
+// cubic lattices; a mesh whose kinds differ more overfills some buckets, one whose
+// kinds are well mixed pays for buckets less full than they could be.  (Local
+// labels, us: element relation of 90^3 pyramid cells 493 at 92 % and 257 at 56 %;
+// hybrid mesh of 4 M ids 353 at 80 % and 181 at 45 %.  Shuffled labels: 90^3 208
+// and 209, 60^3 65 and 74, the hybrid mesh 195 and 210.)
 constexpr int BK_FULL = 92, BK_FULL_PYRAMID = 56, BK_FULL_MIXED = 45;
 constexpr int bk_full(int32_t etype) { return etype == MESH_PYRAMID5 ? BK_FULL_PYRAMID : BK_FULL; }
 // Most buckets of a mesh that would fill the GPU with large tiles but has too many

@@ -21,7 +21,7 @@
 // the short runs that neighbouring tiles of one XCD write side by side meet in
 // that XCD's L2 and leave it as whole lines.  (25.1 M 12-byte records into
 // 2048 buckets on MI355X: 154 us this way, 220 us with each block keeping a
-// contiguous share of every bucket.)  The order is only a matter of speed.
+// contiguous share of every bucket; the 3582 that 8.4 M triangles get: 168 us.)  The order is only a matter of speed.
 #pragma once
 
 #include "common.hpp"
@@ -88,8 +88,10 @@ struct BkLookback {
 
 // Blocks that share a bucket of n records.  Up to cap of them fit one block's
 // LDS.  Beyond, every share reads all of the bucket's records (to count them by
-// vertex, and to pick its own), so their number is bounded: 128 blocks that
-// read together are near what the caches give (about 50 GB/s each).
+// vertex, and to pick its own), so more of them sort more at a time and read more
+// in all: 6 M records of 250 vertices took 11.6 / 7.6 / 5.4 / 8.2 / 17.8 ms with up
+// to 32 / 64 / 128 / 256 / 512 shares, 600,000 of 250 vertices 1.7 / 1.1 / 0.8 /
+// 0.8 / 0.8 ms.
 constexpr uint32_t BK_SHARES = 128;
 __host__ __device__ inline uint32_t bk_shares(uint32_t n, uint32_t cap) {
     return n <= cap ? 1u : tmin((n - 1) / (cap / 2) + 1, BK_SHARES);
@@ -224,7 +226,8 @@ __device__ __forceinline__ uint32_t bk_count(uint32_t* s, uint32_t b, bool valid
 // Block h = 8 k + x takes the tiles x + 8 (R k + r), r < R, in order; before
 // each it writes down its counts so far (within), at the end all of them
 // (btot).  A thread takes whole elements.  Bound by reading conn and by the
-// LDS adds: 8.4 M triangles, 2048 buckets in 22 us (100 MB in, 11 MB out).
+// LDS adds: 8.4 M triangles, 3582 buckets in 38 us (100 MB in, 26 MB out);
+// 2 M with local labels 26 us, lanes of a wave in the same few counters.
 template <int ET, int BLOCK, int EPT>
 __global__ __launch_bounds__(BLOCK) void bk_hist_kernel(const int32_t* __restrict__ conn, int64_t n_elem, BkMap mp,
                                                        int64_t n_tiles, int R, uint16_t* __restrict__ within,
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(BLOCK) void bk_hist_kernel(const int32_t* __restric
 // (by ticket) takes 16 buckets, 64 threads per bucket, each a run of blocks
 // held in registers; the blocks' sums meet in a decoupled look-back.  (A last
 // block that scanned all totals needed device-wide fences, each a write-back
-// of an L2: 68 instead of 9 us on 2560 buckets x 392 blocks.)  Block 0 sets
+// of an L2: 68 instead of 9 us on 2560 buckets x 392 blocks; 11 us on 3582 x 456.)  Block 0 sets
 // the error word and the repeat flag from what bk_hist found.
 constexpr int BKS_BLOCK = 1024;
 constexpr int BKS_COLS = 16;
