@@ -45,7 +45,7 @@ void bk_batch_rows_kernel(BkRowsArgs all, const BkMesh* __restrict__ mesh, const
         if (all.erp) a.erp = all.erp + m.vert_off;
         const uint32_t b = bucket - m.bucket0;
         const uint32_t lo = bk_first_vertex(b, m.mp.mul);
-        const uint32_t hi = b + 1 == m.mp.n_bucket ? (uint32_t)m.mp.n_vert : bk_first_vertex(b + 1, m.mp.mul);
+        const uint32_t hi = b + 1 == m.mp.n_bucket ? (uint32_t)m.mp.n_vert : bk_next_first_vertex(lo, b, m.mp.mul);
         const uint32_t r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)all.starts[bucket]);
         const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)all.starts[bucket + 1]) - r0;
         const uint32_t rec0 = r0 - (uint32_t)__builtin_amdgcn_readfirstlane((int)all.starts[m.bucket0]);

@@ -1174,7 +1174,7 @@ void bk_rows_kernel(BkRowsArgs a) {
         uint32_t mul = a.mp.mul;
         asm volatile("" : "+s"(mul));  // (as bk_tid)
         const uint32_t lo = bk_first_vertex(u.bucket, mul);
-        const uint32_t hi = u.bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_first_vertex(u.bucket + 1, mul);
+        const uint32_t hi = u.bucket + 1 == a.mp.n_bucket ? (uint32_t)a.mp.n_vert : bk_next_first_vertex(lo, u.bucket, mul);
         bk_unit_rows<K, W, LARGE>(a, u, r0, n, r0, lo, (int)(hi - lo), odd, s_all, s_tmp, &s_base);
         if (n_unit == a.mp.n_bucket) return;  // (a block per bucket)
         __syncthreads();                      // before the LDS is used again

@@ -75,6 +75,12 @@ struct BkElem {
 __host__ __device__ inline uint32_t bk_first_vertex(uint32_t bucket, uint32_t mul) {
     return (uint32_t)((((uint64_t)bucket << 32) + mul - 1) / mul);
 }
+// The next bucket's, from this one's (lo): one division, and of 32 bits.
+__host__ __device__ inline uint32_t bk_next_first_vertex(uint32_t lo, uint32_t bucket, uint32_t mul) {
+    const uint32_t width = 0xffffffffu / mul;  // 2^32 / mul, or one less where mul divides it
+    const uint64_t next = (uint64_t)(lo + width) * mul, end = (uint64_t)(bucket + 1) << 32;
+    return lo + width + (next < end ? 1u : 0u);
+}
 __device__ __forceinline__ uint32_t bk_bucket(uint32_t v, uint32_t mul) { return __umulhi(v, mul); }
 
 // bk_rows' look-backs, a word per unit each: node entries, and, within a shared
@@ -352,8 +358,12 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
         const uint32_t b = block * BKS_COLS + lane;
         const bool have = lane < BKS_COLS && b < n_bucket;
         const uint32_t t = have ? s_tot[lane] : 0u;
-        const uint32_t more = have ? bk_shares(t, bucket_cap) - 1 : 0u;
-        const uint64_t mine = (uint64_t)more << 32 | t, incl = (uint64_t)bk_wave_sum(more) << 32 | bk_wave_sum(t);
+        uint32_t more = 0, more_incl = 0;
+        if (__ballot(t > bucket_cap)) {  // (seldom, and a division)
+            more = bk_shares(t, bucket_cap) - 1;
+            more_incl = bk_wave_sum(more);
+        }
+        const uint64_t mine = (uint64_t)more << 32 | t, incl = (uint64_t)more_incl << 32 | bk_wave_sum(t);
         const uint64_t all = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(incl >> 32), WAVE - 1) << 32 |
                              (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
         if (lane == 0) lb_store(scan_lb + block, (block == 0 ? LB_INC : LB_AGG) | all);
