@@ -359,7 +359,7 @@ __global__ __launch_bounds__(BKB_SCAN) void bkb_scan_kernel(const BkMesh* __rest
         const int K = bkb_K(m.etype);
         const uint32_t shares = bk_shares(tot, K == 2 ? cap.K2 : K == 3 ? cap.K3 : cap.K4);
         totals[at] = tot;
-        more[at] = shares - 1;
+        if (more) more[at] = shares - 1;
         if (shares > 1) atomicOr(&hdr[HDR_BKB_SHARED], 1u);
         bmesh[at] = (uint32_t)k;
         lookback.clear(at);
@@ -499,39 +499,44 @@ void plan_batch_buckets(int32_t n_mesh, int64_t total_pairs, int64_t total_slots
                                                    bkb_tile_elems(et, bkb_K(et) + 1, (uint32_t)nb_most + 1, p->tile_slots));
     const int64_t n = p->entries;
     p->bucket_most = ceil_div(total_slots, (int64_t)fill_least) + ceil_div(total_vert, (int64_t)vmax_least) + 3 * n;
-    p->unit_most = p->bucket_most;
-    for (int K = 2; K <= 4; ++K)
-        p->unit_most = tmax(p->unit_most, bk_unit_most(p->bucket_most, total_slots, bk_size(K, p->large).cap));
     p->tile_most = ceil_div(total_slots, tile_least) + n;
     p->scan_most = ceil_div(p->bucket_most, (int64_t)BKS_COLS) + n;
     p->cell_most = p->tile_most * (nb_most + 1);
     // K + 1 words per slot: a word, and K: the edges' ends (a pyramid has 16 of them for 20 neighbours)
     p->word_most = total_slots + total_pairs + total_pairs / 4 + 16 * n;
-    size_t off = HEADER_BYTES;
-    auto take = [&](size_t* at, size_t bytes) {
-        *at = off;
-        off += align_up(bytes);
-    };
-    take(&p->off_mesh, (size_t)n * sizeof(BkMesh));
-    take(&p->off_tile0, (size_t)n * 4);
-    take(&p->off_scan0, (size_t)n * 4);
-    take(&p->off_bmesh, (size_t)p->bucket_most * 4);
-    take(&p->off_tmesh, (size_t)p->tile_most * 4);
-    take(&p->off_starts, ((size_t)p->bucket_most + 1) * 4);
-    take(&p->off_units, ((size_t)p->bucket_most + 1) * 4);
-    take(&p->off_rep, (size_t)p->bucket_most * 4);
-    take(&p->off_lb, BkLookback::bytes(p->unit_most));
-    take(&p->off_rec, (size_t)p->word_most * 4);
-    take(&p->off_cells, (size_t)p->cell_most * 4);
-    // the lists of shared buckets over the counts, which are done with by then, if they fit
-    const size_t with_list = tmax(off, p->off_cells + align_up((size_t)total_slots * 4));
-    if (with_list <= limit) {
-        off = with_list;
-        p->off_list = p->off_cells;
+    // (without what the shares of overfull buckets need, if it does not fit with it)
+    for (int shares = 1; shares >= 0 && !p->on; --shares) {
+        p->shares = shares != 0;
+        p->unit_most = p->bucket_most;
+        for (int K = 2; K <= 4 && p->shares; ++K)
+            p->unit_most = tmax(p->unit_most, bk_unit_most(p->bucket_most, total_slots, bk_size(K, p->large).cap));
+        size_t off = HEADER_BYTES;
+        auto take = [&](size_t* at, size_t bytes) {
+            *at = off;
+            off += align_up(bytes);
+        };
+        take(&p->off_mesh, (size_t)n * sizeof(BkMesh));
+        take(&p->off_tile0, (size_t)n * 4);
+        take(&p->off_scan0, (size_t)n * 4);
+        take(&p->off_bmesh, (size_t)p->bucket_most * 4);
+        take(&p->off_tmesh, (size_t)p->tile_most * 4);
+        take(&p->off_starts, ((size_t)p->bucket_most + 1) * 4);
+        if (p->shares) take(&p->off_units, ((size_t)p->bucket_most + 1) * 4);
+        take(&p->off_rep, (size_t)p->bucket_most * 4);
+        take(&p->off_lb, BkLookback::bytes(p->unit_most, p->shares));
+        take(&p->off_rec, (size_t)p->word_most * 4);
+        take(&p->off_cells, (size_t)p->cell_most * 4);
+        // the lists of shared buckets over the counts, which are done with by then, if they fit
+        const size_t with_list = tmax(off, p->off_cells + align_up((size_t)total_slots * 4));
+        p->off_list = 0;
+        if (p->shares && with_list <= limit) {
+            off = with_list;
+            p->off_list = p->off_cells;
+        }
+        p->total = off;
+        p->on = off <= limit && p->scan_most <= INT32_MAX && p->entries <= INT32_MAX && p->cell_most <= UINT32_MAX &&
+                p->word_most / 2 <= UINT32_MAX;
     }
-    p->total = off;
-    p->on = off <= limit && p->scan_most <= INT32_MAX && p->entries <= INT32_MAX && p->cell_most <= UINT32_MAX &&
-            p->word_most / 2 <= UINT32_MAX;
 }
 
 hipError_t run_batch_buckets(const BkBatchPlan& p, const int32_t* conn, const mesh_segment* segs,
@@ -561,10 +566,11 @@ hipError_t run_batch_buckets(const BkBatchPlan& p, const int32_t* conn, const me
     uint32_t* tmesh = (uint32_t*)(w + p.off_tmesh);
     uint32_t* cells = (uint32_t*)(w + p.off_cells);
     uint32_t* starts = (uint32_t*)(w + p.off_starts);
-    uint32_t* units = (uint32_t*)(w + p.off_units);
+    uint32_t* units = p.shares ? (uint32_t*)(w + p.off_units) : nullptr;
     uint32_t* repeats = (uint32_t*)(w + p.off_rep);
-    const BkLookback lookback = BkLookback::at(w + p.off_lb, p.unit_most);
-    const BkbCaps caps{(uint32_t)bk_size(2, p.large).cap, (uint32_t)bk_size(3, p.large).cap, (uint32_t)bk_size(4, p.large).cap};
+    const BkLookback lookback = BkLookback::at(w + p.off_lb, p.unit_most, p.shares);
+    const auto share_cap = [&](int K) { return p.shares ? (uint32_t)bk_size(K, p.large).cap : UINT32_MAX; };
+    const BkbCaps caps{share_cap(2), share_cap(3), share_cap(4)};
     const auto grid = [&](int64_t per_cu) {  // a multiple of the XCDs
         return dim3((unsigned)tmin<int64_t>(ceil_div(p.tile_most, (int64_t)BK_XCDS) * BK_XCDS, per_cu * BK_CUS));
     };

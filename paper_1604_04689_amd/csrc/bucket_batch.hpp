@@ -25,6 +25,7 @@ struct BkMesh {
 struct BkBatchPlan {
     bool on = false;
     bool large = false;      // bucket size (BkShape)
+    bool shares = false;     // overfull buckets are shared by several blocks
     int32_t n_mesh = 0, total_vert = 0, max_vert = 0;
     int64_t total_slots = 0, total_pairs = 0;
     int32_t fill[5] = {};    // records a bucket is planned for, by K

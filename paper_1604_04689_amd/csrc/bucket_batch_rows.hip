@@ -71,7 +71,8 @@ void bk_batch_rows_kernel(BkRowsArgs all, const BkMesh* __restrict__ mesh, const
 hipError_t launch_batch_bucket_rows(const BkBatchPlan& p, int32_t* node_row_ptr, int32_t* node_cols, int64_t node_cap,
                                     int32_t* elem_row_ptr, int32_t* elem_cols, int64_t elem_cap, char* w, hipStream_t s) {
     const BkRowsArgs a{BkMap{}, (const uint32_t*)(w + p.off_rec), (const uint32_t*)(w + p.off_starts),
-                       (const uint32_t*)(w + p.off_units), (const uint32_t*)(w + p.off_rep), BkLookback::at(w + p.off_lb, p.unit_most),
+                       p.shares ? (const uint32_t*)(w + p.off_units) : nullptr, (const uint32_t*)(w + p.off_rep),
+                       BkLookback::at(w + p.off_lb, p.unit_most, p.shares),
                        p.off_list ? (uint32_t*)(w + p.off_list) : nullptr, (uint32_t*)w, node_row_ptr, node_cols,
                        node_cols ? node_cap : 0, elem_row_ptr, elem_cols, elem_cols ? elem_cap : 0, 0};
     const BkMesh* mesh = (const BkMesh*)(w + p.off_mesh);

@@ -219,9 +219,8 @@ hipError_t run_mixed_buckets(const BkPlan& p, const int32_t* conn, const int32_t
                                   (size_t)p.mp.nb_pad * 4, s, c, p.mp, p.n_tiles, p.R, within, btot, flags, scan_lb, n_scan, hdr);
         if (e == hipSuccess)
             e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)n_scan), dim3(BKS_BLOCK), s, btot, p.hist_blocks,
-                       p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags, scan_lb, starts, (uint32_t*)(w + p.off_units),
-                       (uint32_t)bk_size(p.K, p.large).cap, (uint32_t)p.n_slots, BkLookback::at(w + p.off_lb, p.unit_most),
-                       repeats, hdr);
+                       p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags, scan_lb, starts, bk_units(p, w),
+                       bk_share_cap(p), (uint32_t)p.n_slots, bk_lookback(p, w), repeats, hdr);
         if (e == hipSuccess)
             e = launch_shm("mixed_bucket_part", bkx_part_kernel<BLOCK>, dim3((unsigned)p.n_tiles), dim3(BLOCK),
                            bkx_part_lds(BLOCK, p.mp.nb_pad), s, c, p.mp, p.R, (const uint16_t*)within,

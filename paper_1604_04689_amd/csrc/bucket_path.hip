@@ -80,32 +80,33 @@ void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* 
     const int64_t blocks = BK_XCDS * ceil_div(p->n_tiles, (int64_t)BK_XCDS * p->R);
     if (blocks > BK_HIST_MOST) return;
     p->hist_blocks = (int)blocks;
-    size_t off = HEADER_BYTES;
-    p->off_flags = off;
-    off += align_up((size_t)p->hist_blocks * sizeof(uint32_t));
-    p->off_scan = off;
-    off += align_up((size_t)ceil_div(m.n_bucket, BKS_COLS) * sizeof(uint64_t));
-    p->off_starts = off;
-    off += align_up(((size_t)m.n_bucket + 1) * sizeof(uint32_t));
-    p->off_units = off;
-    off += align_up(((size_t)m.n_bucket + 1) * sizeof(uint32_t));
-    p->off_rep = off;
-    off += align_up((size_t)m.n_bucket * sizeof(uint32_t));
-    p->off_lb = off;
-    p->unit_most = bk_unit_most(m.n_bucket, p->n_elem * most_npe, bk_size(p->K, p->large).cap);
-    off += align_up(BkLookback::bytes(p->unit_most));
-    p->off_rec = off;
-    off += align_up(((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
-    p->off_btot = p->off_list = off;
-    off += align_up((size_t)p->hist_blocks * m.nb_pad * sizeof(uint32_t));
-    p->off_within = off;
-    off += align_up((size_t)p->n_tiles * m.nb_pad * sizeof(uint16_t));
-    // the lists of shared buckets over the counts, which are done with by then, if they fit
-    const size_t with_list = tmax(off, p->off_list + align_up((size_t)p->n_slots * sizeof(uint32_t)));
-    if (with_list <= limit) off = with_list;
-    else p->off_list = 0;
-    p->total = off;
-    p->on = off <= limit;
+    for (int shares = 1; shares >= 0 && !p->on; --shares) {
+        p->shares = shares != 0;
+        size_t off = HEADER_BYTES;
+        auto take = [&](size_t* at, size_t bytes) {
+            *at = off;
+            off += align_up(bytes);
+        };
+        take(&p->off_flags, (size_t)p->hist_blocks * sizeof(uint32_t));
+        take(&p->off_scan, (size_t)ceil_div(m.n_bucket, BKS_COLS) * sizeof(uint64_t));
+        take(&p->off_starts, ((size_t)m.n_bucket + 1) * sizeof(uint32_t));
+        if (p->shares) take(&p->off_units, ((size_t)m.n_bucket + 1) * sizeof(uint32_t));
+        take(&p->off_rep, (size_t)m.n_bucket * sizeof(uint32_t));
+        p->unit_most = p->shares ? bk_unit_most(m.n_bucket, p->n_elem * most_npe, bk_size(p->K, p->large).cap) : m.n_bucket;
+        take(&p->off_lb, BkLookback::bytes(p->unit_most, p->shares));
+        take(&p->off_rec, ((size_t)p->n_slots + 1) * p->W * sizeof(uint32_t));  // (an empty last bucket reads one past)
+        take(&p->off_btot, (size_t)p->hist_blocks * m.nb_pad * sizeof(uint32_t));
+        take(&p->off_within, (size_t)p->n_tiles * m.nb_pad * sizeof(uint16_t));
+        // the lists of shared buckets over the counts, which are done with by then, if they fit
+        const size_t with_list = tmax(off, p->off_btot + align_up((size_t)p->n_slots * sizeof(uint32_t)));
+        p->off_list = 0;
+        if (p->shares && with_list <= limit) {
+            p->off_list = p->off_btot;
+            off = with_list;
+        }
+        p->total = off;
+        p->on = off <= limit;
+    }
 }
 
 void plan_buckets(int64_t n_elem, int32_t etype, int32_t n_vert, const Opts& o, bool node, size_t limit, BkPlan* p) {
@@ -148,9 +149,8 @@ hipError_t launch_tiles(const BkPlan& p, const int32_t* conn, char* w, hipStream
     if (e == hipSuccess)
         e = launch("bucket_scan", bk_scan_kernel, dim3((unsigned)ceil_div(p.mp.n_bucket, BKS_COLS)), dim3(BKS_BLOCK), s,
                    btot, p.hist_blocks, p.mp.n_bucket, p.mp.nb_pad, (const uint32_t*)flags,
-                   (uint64_t*)(w + p.off_scan), (uint32_t*)(w + p.off_starts), (uint32_t*)(w + p.off_units),
-                   (uint32_t)bk_size(p.K, p.large).cap, (uint32_t)p.n_slots,
-                   BkLookback::at(w + p.off_lb, p.unit_most), (uint32_t*)(w + p.off_rep), hdr);
+                   (uint64_t*)(w + p.off_scan), (uint32_t*)(w + p.off_starts), bk_units(p, w),
+                   bk_share_cap(p), (uint32_t)p.n_slots, bk_lookback(p, w), (uint32_t*)(w + p.off_rep), hdr);
     if (e != hipSuccess) return e;
     if (p.K == 0)
         return p.W == 1 ? launch_part<ET, 0, 1, LT>(p, conn, w, s) : launch_part<ET, 0, 2, LT>(p, conn, w, s);

@@ -45,7 +45,8 @@ BkSize bk_size(int K, bool large);
 // The buckets of a mesh, `full` percent full on average, and its records' form,
 // for K neighbours a record; false: not for buckets.
 bool plan_bucket_map(int64_t n_elem, int64_t n_slots, int32_t n_vert, int K, int full, BkPlan* p);
-// Tiles of tile_elems elements of up to most_npe nodes and the workspace; sets p->on.
+// Tiles of tile_elems elements of up to most_npe nodes and the workspace (without what
+// shares of overfull buckets need, if it does not fit with it); sets p->on.
 void plan_bucket_layout(int64_t tile_elems, int most_npe, size_t limit, BkPlan* p);
 
 // Meshes of several element types (both relations).
@@ -53,6 +54,9 @@ void plan_mixed_buckets(int64_t n_elem, int64_t n_ids, int32_t n_vert, const Opt
 hipError_t run_mixed_buckets(const BkPlan& p, const int32_t* conn, const int32_t* elem_off, const uint8_t* etypes,
                              int32_t* node_row_ptr, int32_t* node_cols, int64_t node_cap, int32_t* elem_row_ptr,
                              int32_t* elem_cols, int64_t elem_cap, void* ws, hipStream_t s);
+
+// Records from which on a bucket is shared.
+inline uint32_t bk_share_cap(const BkPlan& p) { return p.shares ? (uint32_t)bk_size(p.K, p.large).cap : UINT32_MAX; }
 
 hipError_t launch_bucket_rows(const BkPlan& p, int32_t* node_row_ptr, int32_t* node_cols, int64_t node_cap,
                               int32_t* elem_row_ptr, int32_t* elem_cols, int64_t elem_cap, char* w, hipStream_t s);

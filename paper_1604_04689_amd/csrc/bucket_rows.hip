@@ -35,7 +35,7 @@ BkSize bk_size(int K, bool large) {
 hipError_t launch_bucket_rows(const BkPlan& p, int32_t* node_row_ptr, int32_t* node_cols, int64_t node_cap,
                               int32_t* elem_row_ptr, int32_t* elem_cols, int64_t elem_cap, char* w, hipStream_t s) {
     const BkRowsArgs a{p.mp, (const uint32_t*)(w + p.off_rec), (const uint32_t*)(w + p.off_starts),
-                       (const uint32_t*)(w + p.off_units), (const uint32_t*)(w + p.off_rep), BkLookback::at(w + p.off_lb, p.unit_most),
+                       bk_units(p, w), (const uint32_t*)(w + p.off_rep), bk_lookback(p, w),
                        p.off_list ? (uint32_t*)(w + p.off_list) : nullptr, (uint32_t*)w, node_row_ptr, node_cols, node_cols ? node_cap : 0,
                        elem_row_ptr, elem_cols, elem_cols ? elem_cap : 0, p.n_elem};
     return with_shape(p.K, p.large, [&](auto k, auto l) {

@@ -87,9 +87,15 @@ __device__ __forceinline__ uint32_t bk_bucket(uint32_t v, uint32_t mul) { return
 // bucket that has repeats (of a vertex in an element), element entries.
 struct BkLookback {
     uint64_t *nodes, *elems;
-    __device__ __forceinline__ void clear(uint32_t unit) const { nodes[unit] = elems[unit] = 0; }
-    static size_t bytes(int64_t units) { return (size_t)units * 2 * sizeof(uint64_t); }
-    static BkLookback at(void* p, int64_t units) { return {(uint64_t*)p, (uint64_t*)p + units}; }
+    __device__ __forceinline__ void clear(uint32_t unit) const {
+        nodes[unit] = 0;
+        if (elems) elems[unit] = 0;
+    }
+    // (no element entries where no bucket is shared)
+    static size_t bytes(int64_t units, bool shares) { return (size_t)units * (shares ? 2 : 1) * sizeof(uint64_t); }
+    static BkLookback at(void* p, int64_t units, bool shares) {
+        return {(uint64_t*)p, shares ? (uint64_t*)p + units : nullptr};
+    }
 };
 
 // Blocks that share a bucket of n records.  Up to cap of them fit one block's
@@ -115,6 +121,10 @@ __device__ __forceinline__ uint32_t bk_wave_sum(uint32_t x) {
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
     return x;
 }
+
+// What a plan with or without shares gives the kernels.
+inline uint32_t* bk_units(const BkPlan& p, char* w) { return p.shares ? (uint32_t*)(w + p.off_units) : nullptr; }
+inline BkLookback bk_lookback(const BkPlan& p, char* w) { return BkLookback::at(w + p.off_lb, p.unit_most, p.shares); }
 
 // Largest i in [0, n) with off[i] <= x (off ascending from 0), found by a
 // whole wave, 64 places at a time.
@@ -374,12 +384,12 @@ static __global__ __launch_bounds__(BKS_BLOCK) void bk_scan_kernel(uint32_t* __r
             const uint64_t to = before + incl, from = to - mine;
             const uint32_t u = b + (uint32_t)(from >> 32);
             starts[b] = tmin((uint32_t)from, rec_cap);
-            units[b] = u;
+            if (units) units[b] = u;
             for (uint32_t i = 0; i <= more; ++i) lookback.clear(u + i);
             repeats[b] = 0;  // counted by bk_part
             if (b + 1 == n_bucket) {
                 starts[n_bucket] = tmin((uint32_t)to, rec_cap);
-                units[n_bucket] = u + more + 1;
+                if (units) units[n_bucket] = u + more + 1;
                 hdr[HDR_BK_UNITS] = u + more + 1;
             }
         }

@@ -163,6 +163,7 @@ struct BkPlan {
     int K = 0, W = 0;         // neighbours per record (0: element relation alone), words per record
     bool large = false;       // bucket size (BkShape)
     bool large_tile = false;  // tile size (BkTile)
+    bool shares = false;      // overfull buckets are shared by several blocks
     int64_t n_elem = 0, n_slots = 0;
     int32_t etype = 0;
     BkMap mp;

@@ -69,6 +69,14 @@ def test_concentrated_elements(etype, n_elem, n_vert, power, repeats):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n_elem,n_vert,power", [(574, 583, 6), (995, 1352, 8), (25_521, 94_310, 5), (64_941, 10_213, 2)])
+def test_no_room_for_shares(n_elem, n_vert, power):
+    """Pyramid meshes whose workspace (that of the sorts) just holds the records:
+    one block does an overfull bucket."""
+    _check(concentrated(5, n_elem, n_vert, power, n_elem, True), 5, n_vert, "no room for shares")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n_vert,first,count,size", [
     (1_200_000, 0, 1, 60_000),          # one row over several windows of ids, the first bucket
     (1_200_000, 1_199_997, 3, 30_000),  # the last bucket ends with such rows
