@@ -234,3 +234,41 @@ def test_overlapping_elements_touch_nothing_outside(n):
     for k, t in outs.items():
         assert (t[:guard] == 7).all() and (t[-guard:] == 7).all(), k
     assert (raw[:pad] == 90).all() and (raw[pad + b.ws_bytes:] == 90).all()
+
+
+@pytest.mark.gpu
+def test_graph_replays_and_two_streams():
+    """Replays of a captured build over an even mesh, an uneven one and the even
+    one again (shares come and go), with an eager build of an uneven mesh on
+    another stream beside each."""
+    import torch
+
+    import paper_1604_04689_amd as nb
+    n_vert, size = 150_000, 40_000
+    uneven = torch.as_tensor(hubs(n_vert, 0, 30, 3000, 2 * size, 1)[:3 * size]).to("cuda:0")
+    rng = np.random.default_rng(2)
+    even = np.stack([rng.permutation(n_vert)[:3 * size] for _ in range(3)], 1)
+    even = even[(even[:, 0] != even[:, 1]) & (even[:, 0] != even[:, 2]) & (even[:, 1] != even[:, 2])]
+    n = min(len(even), len(uneven))
+    inputs = [torch.as_tensor(even[:n].astype(np.int32)).to("cuda:0"), uneven[:n].contiguous()]
+    want = []
+    for c in inputs:
+        node, elem = nb.neighbors(c, 0, n_vert, options=SORTED)
+        want.append([*node, *elem])
+    conn = inputs[0].clone()
+    captured, eager = (nb.NeighborBuild("both", n, 0, n_vert, "cuda:0") for _ in range(2))
+    graph = captured.capture(conn)
+    side = torch.cuda.Stream()
+    for k in (0, 1, 0, 1, 1, 0):
+        print(f"[shares] replay over input {k}", flush=True)
+        conn.copy_(inputs[k])
+        torch.cuda.synchronize()
+        graph.launch()
+        eager.launch(inputs[1], side)
+        node, elem = captured.result()
+        _equal([*node, *elem], want[k], ("replay", k))
+        node, elem = eager.result(side)
+        torch.cuda.synchronize()
+        _equal([*node, *elem], want[1], "beside")
+        captured.row_ptr.zero_(), captured.cols.zero_(), captured.elem_cols.zero_()
+    graph.destroy()
